@@ -596,7 +596,7 @@ int mdls_batch_plan(int p, int count, const mdls_batch_desc *h_desc, void *ws, s
         if (d.n < 1 || d.m < d.n || d.m > kBatchRows || d.a_off < 0 || d.b_off < 0 || d.x_off < 0) return -3;
         plan[(size_t)i] = BatchDesc{d.m, d.n, d.a_off, d.b_off, d.x_off, i, 1};
     }
-    const std::vector<int> slots = batch_schedule(plan);
+    const std::vector<int> slots = batch_schedule(p, plan);
     const int nslots = (int)slots.size();
     const BatchLayout L = batch_layout(p, count);
     char *w = (char *)ws;

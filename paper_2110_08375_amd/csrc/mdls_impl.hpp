@@ -23,9 +23,12 @@
 // arithmetic.
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <functional>
+#include <queue>
 #include <vector>
 
 #pragma once
@@ -846,9 +849,8 @@ __global__ __launch_bounds__(kThreads) void k_apply_u(ApplyArgs g)
 // ============================================================================ batched solves
 // Many independent least-squares problems (m <= kBatchRows) in one persistent launch.  Each
 // workgroup takes the next slot from a counter; a slot names a problem and a member index.
-// The plan lists the problems largest m n^2 first and gives the largest a team of T
-// workgroups (T consecutive slots at the head of the list, so every team is resident from
-// the start), the others one.  A team solves its problem with narrow Householder panels
+// The plan lists the problems longest first and gives the longer ones a team of T workgroups
+// (T consecutive slots; batch_schedule), the others one.  A team solves its problem with narrow Householder panels
 // (panel_run with T workgroups and the team's own barrier counters and exchange slots), the
 // update of the columns right of the panel and of b split over the team's waves (one column
 // per wave), a team barrier after each step, and member 0 does the back substitution of
@@ -856,7 +858,6 @@ __global__ __launch_bounds__(kThreads) void k_apply_u(ApplyArgs g)
 // times (wall clock ticks) are recorded per problem.
 constexpr int kBatchRows = 512;
 constexpr int kTeamMax = 16;      // most workgroups on one problem
-constexpr int kTeamSlots = 128;   // most workgroups in teams (T > 1) per batch
 constexpr int kTeamCtrs = 2 + kBatchRows / 4;  // team barrier + one counter per panel (W >= 4)
 
 struct BatchDesc {
@@ -2430,30 +2431,95 @@ inline BatchLayout batch_layout(int P, int count)
     return L;
 }
 
-// Order and teams of a batch: problems largest m n^2 first (longest processing time
-// first); a problem whose work (m n^2 - n^3/3 multiply-adds) is at least twice the average
-// work per resident workgroup (total / 2 kCUs) gets that many workgroups, at most kTeamMax,
-// while at most kTeamSlots workgroups are in teams.  Returns the slot list (problem index
-// in the sorted plan * kTeamMax + member).
-inline std::vector<int> batch_schedule(std::vector<BatchDesc> &plan)
+// Predicted milliseconds of one m x n problem on a team of T workgroups (one per CU): a column's
+// serial chain (longer where a team meets) plus the multiply-adds shared by the team.  The constants
+// are fitted to single problems and to 256 and 512 equal ones of 64 x 64 to 512 x 512, T = 1 and 16,
+// on MI355X (dd 512 x 512: 28.7 ms on one workgroup, 5.0 on 16; qd 128 and 14.9), and hold within 15 %.
+struct BatchCost {
+    double one, chain, shared;  // T = 1; T > 1: chain + shared / T
+};
+
+inline BatchCost batch_cost(int P, const BatchDesc &d)
 {
-    auto work = [](const BatchDesc &d) { return (double)d.m * d.n * d.n - (double)d.n * d.n * d.n / 3.0 + d.n; };
-    std::stable_sort(plan.begin(), plan.end(), [&](const BatchDesc &x, const BatchDesc &y) { return work(x) > work(y); });
-    double total = 0.0;
-    for (const BatchDesc &d : plan) total += work(d);
-    const double per = total / (2.0 * kCUs);
-    int used = 0;
-    std::vector<int> slots;
-    for (size_t q = 0; q < plan.size(); ++q) {
-        int t = (int)(work(plan[q]) / per);
-        if (t > kTeamMax) t = kTeamMax;
-        if (t < 2 || used + t > kTeamSlots)
-            t = 1;
-        else
-            used += t;
-        plan[q].team = t;
-        for (int k = 0; k < t; ++k) slots.push_back((int)q * kTeamMax + k);
+    const double m = d.m, n = d.n;
+    const double fmas = m * n * n - n * n * n / 3.0 + 2.0 * m * n + n * n / 2.0;
+    const double shared = (P == 2 ? 0.30e-6 : 1.35e-6) * fmas;
+    return BatchCost{(P == 2 ? 4.0e-3 : 14e-3) * n + shared, (P == 2 ? 6.3e-3 : 14e-3) * n, shared};
+}
+
+// Order and teams of a batch.  For a deadline D every problem gets the smallest team (at most
+// kTeamMax workgroups) that is predicted to finish within D, the problems are listed longest first,
+// and the list is played through on kCUs workgroups (the members of a team take consecutive slots,
+// and the team starts with its last member).  Of a falling sequence of deadlines, from every problem
+// alone to every problem on its largest team, the plan with the shortest predicted end is kept; the
+// first one is kept at once where single workgroups already balance (many problems).  A fixed cap on
+// the workgroups in teams, in place of this, left the problems past the first eight of a batch of
+// 160 on one workgroup each: qd, 160 problems of up to 512 x 512, 61.3 ms against 16.2 ms now; dd, 512
+// problems, 15.3 against 9.6 ms.
+// Teams may stand anywhere in the list: slots are taken in order, so at any time at most one team
+// is incomplete, its waiting members are fewer than the resident workgroups, and every complete
+// team finishes without waiting for a later slot.  The members that come first wait until a running
+// problem ends, at most about 0.13 s (qd 512 x 512 on one workgroup); the barrier's default spin
+// limit is some seconds of polls.
+// Returns the slot list (problem index in the sorted plan * kTeamMax + member).
+inline std::vector<int> batch_schedule(int P, std::vector<BatchDesc> &plan)
+{
+    constexpr int kDeadlines = 16;
+    const size_t cnt = plan.size();
+    std::vector<int> team(cnt), best_team, order(cnt), best_order;
+    std::vector<double> t(cnt);
+    std::vector<BatchCost> cost(cnt);
+    double hi = 0.0, lo = 0.0, area = 0.0, best = 0.0;
+    for (size_t q = 0; q < cnt; ++q) {
+        cost[q] = batch_cost(P, plan[q]);
+        hi = std::max(hi, cost[q].one);
+        lo = std::max(lo, cost[q].chain + cost[q].shared / kTeamMax);
+        area += cost[q].one;
     }
+    for (int k = 0; k < kDeadlines; ++k) {
+        const double D = hi * std::pow(lo / hi, (double)k / (kDeadlines - 1));
+        for (size_t q = 0; q < cnt; ++q) {
+            const BatchCost &c = cost[q];
+            team[q] = 1;
+            t[q] = c.one;
+            if (c.one > D) {
+                const double T = (D > c.chain) ? std::ceil(c.shared / (D - c.chain)) : (double)kTeamMax;
+                team[q] = (int)std::min((double)kTeamMax, std::max(2.0, T));
+                t[q] = c.chain + c.shared / team[q];
+            }
+            order[q] = (int)q;
+        }
+        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return t[x] > t[y]; });
+        // the workgroups' times at which they come free, earliest on top
+        std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
+        for (int w = 0; w < kCUs; ++w) free_at.push(0.0);
+        double end = 0.0;
+        for (int q : order) {
+            double start = 0.0;
+            for (int w = 0; w < team[q]; ++w) {
+                start = free_at.top();
+                free_at.pop();
+            }
+            for (int w = 0; w < team[q]; ++w) free_at.push(start + t[q]);
+            end = std::max(end, start + t[q]);
+            if (k > 0 && end >= best) break;  // no better than the plan kept so far
+        }
+        if (k == 0 || end < best) {
+            best = end;
+            best_team = team;
+            best_order = order;
+        }
+        if (k == 0 && end <= 1.05 * area / kCUs) break;
+    }
+    std::vector<BatchDesc> sorted;
+    std::vector<int> slots;
+    sorted.reserve(cnt);
+    for (size_t q = 0; q < cnt; ++q) {
+        sorted.push_back(plan[best_order[q]]);
+        sorted.back().team = best_team[best_order[q]];
+        for (int w = 0; w < sorted.back().team; ++w) slots.push_back((int)q * kTeamMax + w);
+    }
+    plan.swap(sorted);
     return slots;
 }
 

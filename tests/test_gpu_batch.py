@@ -214,3 +214,24 @@ def test_batched_graph_replay(M):
         torch.cuda.synchronize()
         assert np.array_equal(xg.cpu().numpy(), ref), rep
         assert np.all(info.cpu().numpy() == 0)
+
+
+@pytest.mark.parametrize("P,count,m_lo,m_hi", [(2, 1, 200, 200), (2, 24, 16, 200), (2, 90, 96, 160), (4, 3, 40, 150),
+                                               (4, 90, 64, 128), (2, 700, 4, 48)])
+def test_batched_team_plans(M, orc, P, count, m_lo, m_hi):
+    """Batches whose plans have teams of every size (one problem on the largest team, a few uneven
+    ones, more workgroups in teams than the device holds at once) and one without teams:
+    b = A ones formed exactly, x must be ones, in every kernel variant."""
+    print("case batched plan P=%d count=%d" % (P, count), flush=True)
+    shapes = mdgen.batch_shapes(count, 50 + count, m_lo=m_lo, m_hi=m_hi, n_lo=max(1, m_lo // 2))
+    descs, A, b, x_len, mats = make_batch(M, P, shapes, 800, lambda k, Ak: orc.rhs_for(Ak, mdgen.md_ones(P, Ak.shape[1])))
+    kap = [float(np.linalg.cond(Ak[0].T)) for Ak, _ in mats]
+    ws = M.batch_workspace(P, count, dev())
+    M.batch_plan(P, descs, ws)
+    for v in range(M.batch_variants(P)):
+        xg, info = run_batch(M, P, descs, A, b, x_len, v, ws)
+        assert np.all(info == 0), (v, info)
+        for k, (m, n) in enumerate(shapes):
+            err = md_err(x_of(M, descs, xg, P, k), mdgen.md_ones(P, n))
+            assert err <= TOL[P] * max(1.0, kap[k]), (v, k, m, n, err, kap[k])
+            assert err <= 64 * n * unit(P) * max(1.0, kap[k]), (v, k, m, n, err, kap[k])
