@@ -153,17 +153,25 @@ MDQ V<P> renorm(double (&x)[N])
         for (int i = P; i < N; ++i) eps += x[i];
         r.x[P - 1] = eps;
         // Exact cancellation at the top leaves zero limbs between nonzero ones (e.g.
-        // [s, 0, e, 0]); move them to the end (odd-even transposition, branch-free) so that
-        // limb 0 always leads and truncation keeps the significant limbs.
+        // [s, 0, e, 0]); move them to the end (odd-even transposition) so that limb 0 always
+        // leads and truncation keeps the significant limbs.  A zero above the last limb is rare
+        // in computed values and the P passes are as long as the three sums above (5 instructions
+        // a pair, P (P - 1) / 2 pairs), so one minimum over the magnitudes decides whether any
+        // lane needs them; without a zero they change nothing.
+        double least = __builtin_fabs(r.x[0]);
 #pragma unroll
-        for (int pass = 0; pass < P; ++pass) {
+        for (int i = 1; i < P - 1; ++i) least = __builtin_fmin(least, __builtin_fabs(r.x[i]));
+        if (least == 0.0) {
 #pragma unroll
-            for (int i = pass & 1; i + 1 < P; i += 2) {
-                const bool z = (r.x[i] == 0.0);
-                const double hi = z ? r.x[i + 1] : r.x[i];
-                const double lo = z ? 0.0 : r.x[i + 1];
-                r.x[i] = hi;
-                r.x[i + 1] = lo;
+            for (int pass = 0; pass < P; ++pass) {
+#pragma unroll
+                for (int i = pass & 1; i + 1 < P; i += 2) {
+                    const bool z = (r.x[i] == 0.0);
+                    const double hi = z ? r.x[i + 1] : r.x[i];
+                    const double lo = z ? 0.0 : r.x[i + 1];
+                    r.x[i] = hi;
+                    r.x[i + 1] = lo;
+                }
             }
         }
     }
