@@ -1615,31 +1615,6 @@ __global__ __launch_bounds__(kThreads) void k_bs_upd(const double *Rc, long ldr,
 }
 
 // ============================================================================ T, W, Q^T B helpers
-// G(l, j) = y_l^T y_j (l < j) for tile block k: block (j, k), one wave per l.
-template <int P>
-__global__ __launch_bounds__(kThreads) void k_gram(const double *A, long lda, long ps, int m, int tile, double *G,
-                                                  long gps)
-{
-    const int j = blockIdx.x, k = blockIdx.y;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const long kt = (long)k * tile;
-    const double *Y = A + kt * lda + kt;
-    const int h = m - (int)kt;
-    double *Gk = G + kt * tile;
-    for (int l = wid; l < tile; l += 4) {
-        if (l >= j) {
-            if (lane == 0) stm(Gk, gps, (long)j * tile + l, zero<P>());
-            continue;
-        }
-        Acc<P> acc = acc_zero<P>();
-        int nt = 0;
-        for (int r = j + lane; r < h; r += 64)  // y_j is zero above row j
-            acc_fma_step(acc, y_entry<P>(Y, lda, ps, r, l, h, tile), y_entry<P>(Y, lda, ps, r, j, h, tile), nt++);
-        const V<P> s = wave_sum(acc_get(acc));
-        if (lane == 0) stm(Gk, gps, (long)j * tile + l, s);
-    }
-}
-
 // W(r, k*tile + j) = -sum_{l<=j} Y_k(r, l) T_k(l, j) for r >= k*tile; zero above.
 template <int P>
 __global__ __launch_bounds__(kThreads) void k_form_w(const double *A, long lda, long ps, const double *T, long ldt,
@@ -1679,31 +1654,239 @@ __global__ __launch_bounds__(kThreads) void k_tn(const double *Y, long lda, long
     if (lane == 0) stm(S, sps, (long)c * tile + l, s);
 }
 
-// U(i, c) = sum_{l<=i} T(l, i) S(l, c), written over S (U in a separate buffer)
-template <int P>
-__global__ __launch_bounds__(kThreads) void k_trmm_t(const double *T, long ldt, long tps, const double *S, long sps,
+// The products of a few columns (fewer than kGemmCols): U(i, c) = sum_l op(T)(i, l) S(l, c), one
+// wave per (i, c), the lanes over l (op(T) = T^T: l <= i, or T: l >= i).  One thread per output with
+// its chain of tile multiply-adds took 13.6 us for one dd column and tile 128; this takes 3.2.
+template <int P, bool TRANS>
+__global__ __launch_bounds__(kThreads) void k_trmm_v(const double *T, long ldt, long tps, const double *S, long sps,
                                                     double *U, int tile, int nrhs, const int *skip)
 {
     if (skip && *skip) return;
-    const int i = blockIdx.x * kThreads + threadIdx.x, c = blockIdx.y;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int i = blockIdx.x * 4 + wid, c = blockIdx.y;
     if (i >= tile || c >= nrhs) return;
     Acc<P> acc = acc_zero<P>();
-    for (int l = 0; l <= i; ++l) acc_fma_step(acc, ldm<P>(T, tps, (long)i * ldt + l), ldm<P>(S, sps, (long)c * tile + l), l);
-    stm(U, sps, (long)c * tile + i, acc_get(acc));
+    int nt = 0;
+    for (int l = TRANS ? lane : i + lane; l < (TRANS ? i + 1 : tile); l += 64)
+        acc_fma_step(acc, ldm<P>(T, tps, TRANS ? (long)i * ldt + l : (long)l * ldt + i),
+                     ldm<P>(S, sps, (long)c * tile + l), nt++);
+    const V<P> s = wave_sum(acc_get(acc));
+    if (lane == 0) stm(U, sps, (long)c * tile + i, s);
 }
 
-// U(i, c) = sum_{l>=i} T(i, l) S(l, c) (T upper triangular, applied without transposition)
+// B(r, c) -= sum_l Y(r, l) U(l, c) for a few columns: 64 rows of one column per workgroup, the
+// columns of Y split over the four waves (two accumulators a lane) and combined in a fixed order.
+// One thread per row with its chain of tile multiply-adds (8 workgroups at 2048 rows) took 30.4 us
+// (a mean over the tiles of n = 2048) for one dd column and tile 128; this takes 7.0.
 template <int P>
-__global__ __launch_bounds__(kThreads) void k_trmm_n(const double *T, long ldt, long tps, const double *S, long sps,
-                                                    double *U, int tile, int nrhs, const int *skip)
+__global__ __launch_bounds__(kThreads) void k_nn_sub_v(const double *Y, long lda, long ps, int h, int tile,
+                                                      const double *U, long ups, double *B, long ldb, long bps,
+                                                      const int *skip)
 {
+    __shared__ double su[256 * P];
+    __shared__ double sp[4][64 * P];
     if (skip && *skip) return;
-    const int i = blockIdx.x * kThreads + threadIdx.x, c = blockIdx.y;
-    if (i >= tile || c >= nrhs) return;
-    Acc<P> acc = acc_zero<P>();
-    for (int l = i; l < tile; ++l)
-        acc_fma_step(acc, ldm<P>(T, tps, (long)l * ldt + i), ldm<P>(S, sps, (long)c * tile + l), l - i);
-    stm(U, sps, (long)c * tile + i, acc_get(acc));
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, c = blockIdx.y;
+    for (int l = threadIdx.x; l < tile; l += kThreads) lds_st(&su[l * P], ldm<P>(U, ups, (long)c * tile + l));
+    __syncthreads();
+    const long r = (long)blockIdx.x * 64 + lane;
+    const int q = (tile + 3) / 4;
+    const int lb = wid * q, le = min(tile, lb + q);
+    constexpr int NA = 2;
+    Acc<P> acc[NA];
+#pragma unroll
+    for (int a = 0; a < NA; ++a) acc[a] = acc_zero<P>();
+    int nt = 0;
+    for (int l = lb; l < le; l += NA) {
+        V<P> y[NA];
+#pragma unroll
+        for (int k = 0; k < NA; ++k) y[k] = (l + k < le) ? y_entry<P>(Y, lda, ps, r, l + k, h, tile) : zero<P>();
+#pragma unroll
+        for (int k = 0; k < NA; ++k)
+            if (l + k < le) acc_fma(acc[k], y[k], lds_ld<P>(&su[(l + k) * P]));
+        if ((++nt) % kLazy<P> == 0) {
+#pragma unroll
+            for (int a = 0; a < NA; ++a) acc[a] = acc_from(acc_get(acc[a]));
+        }
+    }
+    acc_add_acc(acc[0], acc[1]);
+    lds_st(&sp[wid][lane * P], acc_get(acc[0]));
+    __syncthreads();
+    if (wid == 0 && r < h) {
+        V<P> v = lds_ld<P>(&sp[0][lane * P]);
+        for (int w = 1; w < 4; ++w) v = add(v, lds_ld<P>(&sp[w][lane * P]));
+        stm(B, bps, (long)c * ldb + r, sub(ldm<P>(B, bps, (long)c * ldb + r), v));
+    }
+}
+
+// The same three products, and the Gram block of a tile, for many columns: Out(i, c) =
+// [Out(i, c) -] sum_k X(i, k) Z(k, c), a workgroup per block of 16 RB x 16 RB outputs, each thread
+// RB x RB of them (rows i = tx + 16 a, columns c = ty + 16 b).  Chunks of 16 k of X and Z are staged
+// in LDS, the next chunk's loads in flight during the current one's multiply-adds; a thread's
+// multiply-adds take 2 P RB LDS words for RB^2 of them.  dd (12 instructions a multiply-add) needs
+// RB = 2 to stay below the LDS rate, qd and od (108, 952) do not.  Sums are kept in two levels (64
+// terms, then the sums), so that the error grows as slowly as in a wave's butterfly.
+//   kTN    S = Y^T B          X(i, k) = Y(k, i)
+//   kTT    U = T^T S          X(i, k) = T(k, i), k <= i
+//   kTNo   U = T S            X(i, k) = T(i, k), k >= i
+//   kNN    B -= Y U           X(i, k) = Y(i, k)
+//   kGram  G = striu(Y^T Y)   as kTN with Z = Y; tile block blockIdx.z
+// A block skips the k where its X is zero.  Bound by the FP64 instruction rate: qd, m = n = 1024,
+// tile 128, all 1024 columns, 2.31 ms for the eight Y^T B, 2.17 for B -= Y U and 0.54 for T S, 72 to
+// 77 % of that rate for the first two (one wave per (l, c), one thread per row and one thread per (i, c)
+// before, 64 columns at a time: 4.66, 9.77 and 10.2 ms).
+enum { kTN, kTT, kTNo, kNN, kGram };
+constexpr int kGemmCols = 16;  // fewer columns take the wave-per-output kernels
+
+struct GemmArgs {
+    const double *X;  // Y (unit lower trapezoidal, h x tile) or T
+    long ldx, psx;
+    const double *Z;
+    long ldz, psz;
+    double *O;
+    long ldo, pso;
+    int h, tile, nc;
+    long xstep, ostep;  // kGram: tile block t at X + t xstep (h - t tile rows), O + t ostep
+    const int *skip;
+};
+
+template <int P>
+constexpr int gemm_rb()
+{
+    return P <= 2 ? 2 : 1;
+}
+
+template <int P, int MODE>
+__global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g)
+{
+    constexpr int RB = gemm_rb<P>(), BT = 16 * RB, KC = 16;
+    constexpr int LD = BT * P + 2;  // doubles per staged k (the 2 keep the staging stores off one bank)
+    __shared__ double sX[2][KC * LD];
+    __shared__ double sZ[2][KC * LD];
+    if (g.skip && *g.skip) return;
+    const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
+    const int i0 = blockIdx.x * BT, c0 = blockIdx.y * BT;
+    const double *X = g.X;
+    double *O = g.O;
+    int h = g.h;
+    if constexpr (MODE == kGram) {
+        X += (long)blockIdx.z * g.xstep;
+        O += (long)blockIdx.z * g.ostep;
+        h -= (int)blockIdx.z * g.tile;
+    }
+    const int mo = (MODE == kNN) ? h : g.tile;                 // rows of the output
+    const int nc = (MODE == kGram) ? g.tile : g.nc;
+    // the k with X(i, k) not zero for some i of the block
+    int kb = 0, ke = (MODE == kTN || MODE == kGram) ? h : g.tile;
+    if constexpr (MODE == kTN || MODE == kTNo) kb = i0;
+    if constexpr (MODE == kGram) kb = (c0 > i0) ? c0 : i0;     // y_j is zero above row j
+    if constexpr (MODE == kTT || MODE == kNN) ke = (i0 + BT < ke) ? i0 + BT : ke;
+    if constexpr (MODE == kGram) {
+        if (i0 >= c0 + BT) ke = kb;  // below the diagonal: zeros
+    }
+    auto xval = [&](int i, int k) __attribute__((always_inline)) {
+        if constexpr (MODE == kTN || MODE == kGram) {
+            return y_entry<P>(X, g.ldx, g.psx, k, i, h, g.tile);
+        } else if constexpr (MODE == kNN) {
+            return neg(y_entry<P>(X, g.ldx, g.psx, i, k, h, g.tile));
+        } else if constexpr (MODE == kTT) {
+            return (k <= i && i < g.tile) ? ldm<P>(X, g.psx, (long)i * g.ldx + k) : zero<P>();
+        } else {
+            return (k >= i && k < g.tile) ? ldm<P>(X, g.psx, (long)k * g.ldx + i) : zero<P>();
+        }
+    };
+    auto zval = [&](int k, int c) __attribute__((always_inline)) {
+        if constexpr (MODE == kGram) return y_entry<P>(X, g.ldx, g.psx, k, c, h, g.tile);
+        return (k < ke && c < nc) ? ldm<P>(g.Z, g.psz, (long)c * g.ldz + k) : zero<P>();
+    };
+    // staging: X is contiguous along k for kTN, kTT and kGram, along i for kTNo and kNN; Z along k
+    constexpr bool XK = MODE == kTN || MODE == kTT || MODE == kGram;
+    V<P> xs[RB], zs[RB];
+    auto fetch = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int a = 0; a < RB; ++a) {
+            xs[a] = XK ? xval(i0 + ty + 16 * a, k0 + tx) : xval(i0 + tx + 16 * a, k0 + ty);
+            zs[a] = zval(k0 + tx, c0 + ty + 16 * a);
+        }
+    };
+    auto stage = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int a = 0; a < RB; ++a) {
+            const int xi = (XK ? ty : tx) + 16 * a, xk = XK ? tx : ty;
+            lds_st(&sX[buf][xk * LD + xi * P], xs[a]);
+            lds_st(&sZ[buf][tx * LD + (ty + 16 * a) * P], zs[a]);
+        }
+    };
+    Acc<P> acc[RB][RB], tot[RB][RB];
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            acc[a][b] = acc_zero<P>();
+            const int i = i0 + tx + 16 * a, c = c0 + ty + 16 * b;
+            tot[a][b] = acc_zero<P>();
+            if (MODE == kNN && i < mo && c < nc) tot[a][b] = acc_from(ldm<P>(O, g.pso, (long)c * g.ldo + i));
+        }
+    if (kb < ke) {
+        fetch(kb);
+        stage(0);
+    }
+    __syncthreads();
+    int nch = 0;
+    for (int k0 = kb; k0 < ke; k0 += KC) {
+        const int buf = nch & 1;
+        const bool more = k0 + KC < ke;
+        if (more) fetch(k0 + KC);
+#pragma unroll 1
+        for (int k = 0; k < KC; ++k) {
+            V<P> x[RB], z[RB];
+#pragma unroll
+            for (int a = 0; a < RB; ++a) {
+                x[a] = lds_ld<P>(&sX[buf][k * LD + (tx + 16 * a) * P]);
+                z[a] = lds_ld<P>(&sZ[buf][k * LD + (ty + 16 * a) * P]);
+            }
+#pragma unroll
+            for (int a = 0; a < RB; ++a)
+#pragma unroll
+                for (int b = 0; b < RB; ++b) acc_fma(acc[a][b], x[a], z[b]);
+            if constexpr (kLazy<P> < KC) {
+                if ((k + 1) % kLazy<P> == 0) {
+#pragma unroll
+                    for (int a = 0; a < RB; ++a)
+#pragma unroll
+                        for (int b = 0; b < RB; ++b) acc[a][b] = acc_from(acc_get(acc[a][b]));
+                }
+            }
+        }
+        ++nch;
+        if (nch % 4 == 0 || !more) {
+#pragma unroll
+            for (int a = 0; a < RB; ++a)
+#pragma unroll
+                for (int b = 0; b < RB; ++b) {
+                    acc_add(tot[a][b], acc_get(acc[a][b]));
+                    tot[a][b] = acc_from(acc_get(tot[a][b]));
+                    acc[a][b] = acc_zero<P>();
+                }
+        } else if (kLazy<P> >= KC && kLazy<P> < 64) {
+#pragma unroll
+            for (int a = 0; a < RB; ++a)
+#pragma unroll
+                for (int b = 0; b < RB; ++b) acc[a][b] = acc_from(acc_get(acc[a][b]));
+        }
+        if (more) stage(buf ^ 1);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int a = 0; a < RB; ++a)
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            const int i = i0 + tx + 16 * a, c = c0 + ty + 16 * b;
+            if (i >= mo || c >= nc) continue;
+            V<P> v = acc_get(tot[a][b]);
+            if (MODE == kGram && i >= c) v = zero<P>();
+            stm(O, g.pso, (long)c * g.ldo + i, v);
+        }
 }
 
 namespace {
@@ -1716,22 +1899,6 @@ __global__ void k_identity(double *B, long ldb, long bps, int rows, int cols, in
     for (int k = 0; k < P; ++k) B[k * bps + (long)c * ldb + r] = (k == 0 && r == c) ? 1.0 : 0.0;
 }
 }  // namespace
-
-// B(kt + r, c) -= sum_l Y_k(r, l) U(l, c)
-template <int P>
-__global__ __launch_bounds__(kThreads) void k_nn_sub(const double *Y, long lda, long ps, int h, int tile, const double *U,
-                                                    long ups, double *B, long ldb, long bps, const int *skip)
-{
-    if (skip && *skip) return;
-    const long r = (long)blockIdx.x * kThreads + threadIdx.x;
-    const int c = blockIdx.y;
-    if (r >= h) return;
-    Acc<P> acc = acc_from(ldm<P>(B, bps, (long)c * ldb + r));
-    const long lmax = ((long)tile - 1 < r) ? (long)tile - 1 : r;
-    for (int l = 0; l <= (int)lmax; ++l)
-        acc_fma_step(acc, neg(y_entry<P>(Y, lda, ps, r, l, h, tile)), ldm<P>(U, ups, (long)c * tile + l), l);
-    stm(B, bps, (long)c * ldb + r, acc_get(acc));
-}
 
 // ============================================================================ launch timing
 // When timing is on (mdls_timing_enable), every launch is bracketed by two events on its
@@ -2259,7 +2426,11 @@ int qr_impl(int m, int n, int tile, double *A, int lda, double *beta, double *T,
         const int N = n / tile;
         double *G = cx.big();
         const long gps = (long)tile * n;
-        MDLS_LAUNCH("k_gram", P, 0, (k_gram<P>), dim3(tile, N), dim3(kThreads), s, A, (long)lda, psa, m, tile, G, gps);
+        constexpr int BT = 16 * gemm_rb<P>();
+        const int nb = (tile + BT - 1) / BT;
+        const GemmArgs ga{A, (long)lda, psa, nullptr, 0, 0, G, (long)tile, gps, m, tile, tile, (long)tile * (lda + 1),
+                          (long)tile * tile, nullptr};
+        MDLS_LAUNCH("k_gram", P, 0, (k_gemm<P, kGram>), dim3(nb, nb, N), dim3(kThreads), s, ga);
         InvArgs ia;
         ia.U = G;
         ia.ldu = tile;
@@ -2292,78 +2463,88 @@ int qr_split_t(int m, int n, int tile, double *A, int lda, double *T, int ldt, v
     return qr_impl<P>(m, n, tile, A, lda, nullptr, T, ldt, ws, nullptr, s, split);
 }
 
-// B := Q^T B by the tile blocks in order, B := B - Y_k T_k^T (Y_k^T B), 64 columns of B at a
-// time; S and U are scratch of P tile 64 doubles each.  Every kernel returns at once while
-// *skip is set (skip may be null).
-template <int P>
-void apply_qt_blocks(int m, int n, int tile, const double *A, int lda, const double *T, int ldt, double *B, int ldb,
-                     int nrhs, double *S, double *U, const int *skip, hipStream_t s)
+// One tile block on nc columns of B: S = Y^T B, U = op(T) S, B -= Y U (op(T) = T^T for Q^T, T for Q);
+// h rows from the block's diagonal.  kGemmCols columns or more go in 16 x 16 blocks of outputs (qd, tile
+// 128, n = 1024: 39 us a tile block and 64 columns for the three kernels, 192 with a wave or a thread per
+// output); fewer, where those blocks would be mostly empty, one wave per output.
+template <int P, bool TRANS>
+void apply_block(const double *Y, long lda, long psa, int h, int tile, const double *Tk, long ldt, long tps, double *B,
+                 long ldb, long bps, int nc, double *S, double *U, long sps, const int *skip, hipStream_t s)
+{
+    const double tri = 0.5 * tile * tile * nc, full = (double)h * tile * nc;
+    if (nc < kGemmCols) {
+        MDLS_LAUNCH("k_tn", P, full, (k_tn<P>), dim3((tile + 3) / 4, nc), dim3(kThreads), s, Y, lda, psa, h, tile, B, ldb,
+                    bps, nc, S, sps, skip);
+        MDLS_LAUNCH("k_trmm", P, tri, (k_trmm_v<P, TRANS>), dim3((tile + 3) / 4, nc), dim3(kThreads), s, Tk, ldt, tps, S,
+                    sps, U, tile, nc, skip);
+        MDLS_LAUNCH("k_nn_sub", P, full, (k_nn_sub_v<P>), dim3((h + 63) / 64, nc), dim3(kThreads), s, Y, lda, psa, h, tile,
+                    U, sps, B, ldb, bps, skip);
+        return;
+    }
+    constexpr int BT = 16 * gemm_rb<P>();
+    const unsigned bt = (tile + BT - 1) / BT, bh = (h + BT - 1) / BT, bc = (nc + BT - 1) / BT;
+    const GemmArgs a1{Y, lda, psa, B, ldb, bps, S, (long)tile, sps, h, tile, nc, 0, 0, skip};
+    const GemmArgs a2{Tk, ldt, tps, S, (long)tile, sps, U, (long)tile, sps, h, tile, nc, 0, 0, skip};
+    const GemmArgs a3{Y, lda, psa, U, (long)tile, sps, B, ldb, bps, h, tile, nc, 0, 0, skip};
+    MDLS_LAUNCH("k_tn", P, full, (k_gemm<P, kTN>), dim3(bt, bc), dim3(kThreads), s, a1);
+    MDLS_LAUNCH("k_trmm", P, tri, (k_gemm<P, TRANS ? kTT : kTNo>), dim3(bt, bc), dim3(kThreads), s, a2);
+    MDLS_LAUNCH("k_nn_sub", P, full, (k_gemm<P, kNN>), dim3(bh, bc), dim3(kThreads), s, a3);
+}
+
+// B := Q^T B (TRANS: the tile blocks in order, B := (I - Y_k T_k^T Y_k^T) B) or B := Q B (the blocks
+// in reverse, T untransposed; the paper forms Q itself, Algorithm 2: with B = I this is that Q), cols
+// columns of B at a time; S and U are scratch of P tile cols doubles each.  Every kernel returns at
+// once while *skip is set (skip may be null).
+template <int P, bool TRANS>
+void apply_blocks(int m, int n, int tile, const double *A, int lda, const double *T, int ldt, double *B, int ldb,
+                  int nrhs, double *S, double *U, int cols, const int *skip, hipStream_t s)
 {
     const long psa = (long)lda * n, tps = (long)ldt * n, bps = (long)ldb * nrhs;
-    const long sps = (long)tile * 64;
+    const long sps = (long)tile * cols;
     const int N = n / tile;
-    for (int c0 = 0; c0 < nrhs; c0 += 64) {
-        const int nc = (nrhs - c0 < 64) ? nrhs - c0 : 64;
+    for (int c0 = 0; c0 < nrhs; c0 += cols) {
+        const int nc = (nrhs - c0 < cols) ? nrhs - c0 : cols;
         double *Bc = B + (long)c0 * ldb;
-        for (int k = 0; k < N; ++k) {
-            const long kt = (long)k * tile;
-            const double *Y = A + kt * lda + kt;
-            const int h = m - (int)kt;
-            MDLS_LAUNCH("k_tn", P, (double)h * tile * nc, (k_tn<P>), dim3((tile + 3) / 4, nc), dim3(kThreads), s, Y,
-                        (long)lda, psa, h, tile, Bc + kt, (long)ldb, bps, nc, S, sps, skip);
-            MDLS_LAUNCH("k_trmm_t", P, 0.5 * tile * tile * nc, (k_trmm_t<P>), dim3((tile + kThreads - 1) / kThreads, nc),
-                        dim3(kThreads), s, T + kt * ldt, (long)ldt, tps, S, sps, U, tile, nc, skip);
-            MDLS_LAUNCH("k_nn_sub", P, (double)h * tile * nc, (k_nn_sub<P>), dim3((h + kThreads - 1) / kThreads, nc),
-                        dim3(kThreads), s, Y, (long)lda, psa, h, tile, U, sps, Bc + kt, (long)ldb, bps, skip);
+        for (int q = 0; q < N; ++q) {
+            const long kt = (long)(TRANS ? q : N - 1 - q) * tile;
+            apply_block<P, TRANS>(A + kt * lda + kt, (long)lda, psa, m - (int)kt, tile, T + kt * ldt, (long)ldt, tps,
+                                  Bc + kt, (long)ldb, bps, nc, S, U, sps, skip, s);
         }
     }
+}
+
+// The same with S and U in the workspace: S in the trailing update's partial sums and U in the tile
+// inverses' place where each holds 64 columns or more, else both in the latter, 64 columns each.
+// The more columns a launch has, the more blocks of outputs: qd, m = n = 1024, 1024 columns in chunks
+// of 64 leave 32 blocks for Y^T B.
+template <int P, bool TRANS>
+int apply_ws(int m, int n, int tile, const double *A, int lda, const double *T, int ldt, double *B, int ldb, int nrhs,
+             void *ws, hipStream_t s)
+{
+    Ctx<P> cx{(char *)ws, layout(P, m, n, tile), s};
+    const size_t col = sizeof(double) * P * tile;
+    const size_t cols = std::min((cx.L.anu - cx.L.apart) / col, (cx.L.total - cx.L.big) / col);
+    if (cols >= 64)
+        apply_blocks<P, TRANS>(m, n, tile, A, lda, T, ldt, B, ldb, nrhs, cx.apart(), cx.big(),
+                               (int)std::min(cols, (size_t)nrhs), nullptr, s);
+    else
+        apply_blocks<P, TRANS>(m, n, tile, A, lda, T, ldt, B, ldb, nrhs, cx.big(), cx.big() + (size_t)P * tile * 64, 64,
+                               nullptr, s);
+    return hipGetLastError() == hipSuccess ? 0 : MDLS_EHIP;
 }
 
 template <int P>
 int apply_qt_t(int m, int n, int tile, const double *A, int lda, const double *T, int ldt, double *B, int ldb, int nrhs,
                void *ws, hipStream_t s)
 {
-    Ctx<P> cx{(char *)ws, layout(P, m, n, tile), s};
-    double *S = cx.big();
-    apply_qt_blocks<P>(m, n, tile, A, lda, T, ldt, B, ldb, nrhs, S, S + (size_t)P * tile * 64, nullptr, s);
-    return hipGetLastError() == hipSuccess ? 0 : MDLS_EHIP;
-}
-
-// B := Q B = Q_0 Q_1 ... Q_{N-1} B with Q_k = I - Y_k T_k Y_k^T: the tiles in reverse order,
-// B -= Y_k T_k (Y_k^T B) (the paper forms Q itself, Algorithm 2; with B = I this is that Q).
-// S and U are scratch of P tile 64 doubles each; every kernel returns at once while *skip is set.
-template <int P>
-void apply_q_blocks(int m, int n, int tile, const double *A, int lda, const double *T, int ldt, double *B, int ldb,
-                    int nrhs, double *S, double *U, const int *skip, hipStream_t s)
-{
-    const long psa = (long)lda * n, tps = (long)ldt * n, bps = (long)ldb * nrhs;
-    const long sps = (long)tile * 64;
-    const int N = n / tile;
-    for (int c0 = 0; c0 < nrhs; c0 += 64) {
-        const int nc = (nrhs - c0 < 64) ? nrhs - c0 : 64;
-        double *Bc = B + (long)c0 * ldb;
-        for (int k = N - 1; k >= 0; --k) {
-            const long kt = (long)k * tile;
-            const double *Y = A + kt * lda + kt;
-            const int h = m - (int)kt;
-            MDLS_LAUNCH("k_tn", P, (double)h * tile * nc, (k_tn<P>), dim3((tile + 3) / 4, nc), dim3(kThreads), s, Y,
-                        (long)lda, psa, h, tile, Bc + kt, (long)ldb, bps, nc, S, sps, skip);
-            MDLS_LAUNCH("k_trmm_n", P, 0.5 * tile * tile * nc, (k_trmm_n<P>), dim3((tile + kThreads - 1) / kThreads, nc),
-                        dim3(kThreads), s, T + kt * ldt, (long)ldt, tps, S, sps, U, tile, nc, skip);
-            MDLS_LAUNCH("k_nn_sub", P, (double)h * tile * nc, (k_nn_sub<P>), dim3((h + kThreads - 1) / kThreads, nc),
-                        dim3(kThreads), s, Y, (long)lda, psa, h, tile, U, sps, Bc + kt, (long)ldb, bps, skip);
-        }
-    }
+    return apply_ws<P, true>(m, n, tile, A, lda, T, ldt, B, ldb, nrhs, ws, s);
 }
 
 template <int P>
 int apply_q_t(int m, int n, int tile, const double *A, int lda, const double *T, int ldt, double *B, int ldb, int nrhs,
               void *ws, hipStream_t s)
 {
-    Ctx<P> cx{(char *)ws, layout(P, m, n, tile), s};
-    double *S = cx.big();
-    apply_q_blocks<P>(m, n, tile, A, lda, T, ldt, B, ldb, nrhs, S, S + (size_t)P * tile * 64, nullptr, s);
-    return hipGetLastError() == hipSuccess ? 0 : MDLS_EHIP;
+    return apply_ws<P, false>(m, n, tile, A, lda, T, ldt, B, ldb, nrhs, ws, s);
 }
 
 // Q(:, 0:ncols) := the first ncols columns of Q (m x m orthogonal factor), ld ldq
@@ -2674,7 +2855,7 @@ int refine_t(int m, int n, int tile, const double *A, int lda, const double *b, 
                                 gdd + it0 + tile, (long)n, rest, tile, done);
             }
         }
-        apply_qt_blocks<2>(m, n, tile, F, lda, T, tile, rdd, m, 1, S, U, done, s);
+        apply_blocks<2, true>(m, n, tile, F, lda, T, tile, rdd, m, 1, S, U, 1, done, s);
         if (aug)
             MDLS_LAUNCH("k_aug_split", PX, 0, (k_aug_split<2>), dim3((n + kThreads - 1) / kThreads), dim3(kThreads), s,
                         rdd, (long)m, hdd, (long)n, cx.yw(), (long)n, n, done);
@@ -2685,7 +2866,7 @@ int refine_t(int m, int n, int tile, const double *A, int lda, const double *b, 
         MDLS_LAUNCH("k_refine_add", PX, 0, (k_refine_add<PX, 2>), dim3((n + kThreads - 1) / kThreads), dim3(kThreads), s,
                     x, (long)n, dd, (long)n, n, (unsigned long long *)(norms + 2 * it), done);
         if (aug) {
-            apply_q_blocks<2>(m, n, tile, F, lda, T, tile, rdd, m, 1, S, U, done, s);
+            apply_blocks<2, false>(m, n, tile, F, lda, T, tile, rdd, m, 1, S, U, 1, done, s);
             MDLS_LAUNCH("k_md_add", PX, 0, (k_md_add<PX, 2>), dim3((m + kThreads - 1) / kThreads), dim3(kThreads), s, rr,
                         (long)m, rdd, (long)m, m, done);
         }

@@ -1,0 +1,58 @@
+"""GPU parity of Q^T B and Q B on blocks of columns: the products of many columns are formed in
+blocks of 16 x 16 (32 x 32 in double double) outputs, those of fewer than 16 columns a wave per
+output; both against the oracle's reflectors at the edges of the blocks (tiles, rows and columns
+that are no multiple of 16, one more and one less than a block)."""
+import numpy as np
+import pytest
+
+import mdgen
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def unit(P):
+    return 2.0 ** -(53 * P - (P - 1))
+
+
+def md_err(x, ref):
+    d = np.zeros(ref.shape[1:])
+    for k in range(ref.shape[0] - 1, -1, -1):
+        d = d + (x[k] - ref[k])
+    return np.max(np.abs(d)) / np.max(np.abs(ref[0]))
+
+
+CASES = [
+    # P, m, n, tile, columns of B
+    (2, 300, 96, 48, 33), (2, 65, 40, 20, 16), (2, 70, 64, 64, 15), (2, 45, 45, 45, 32), (2, 40, 31, 31, 1),
+    (4, 90, 60, 20, 17), (4, 130, 100, 100, 64), (4, 260, 256, 256, 31), (4, 33, 9, 1, 18),
+    (8, 50, 24, 12, 16), (8, 40, 33, 33, 40), (8, 70, 64, 64, 3), (1, 100, 48, 16, 50),
+]
+
+
+@pytest.mark.parametrize("P,m,n,tile,nrhs", CASES)
+def test_apply_block_of_columns(orc, P, m, n, tile, nrhs):
+    import paper_2110_08375_amd as M
+
+    print("case apply P=%d m=%d n=%d tile=%d nrhs=%d" % (P, m, n, tile, nrhs), flush=True)
+    A = mdgen.md_uniform(P, m, n, 500 + m, mdgen.STREAM_A)
+    B = mdgen.md_uniform(P, m, nrhs, 600 + m, mdgen.STREAM_B)
+    Ag, Bg = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    T = torch.full((P, n, tile), 7.0, dtype=torch.float64, device="cuda")
+    beta = torch.zeros((P, n), dtype=torch.float64, device="cuda")
+    M.qr(P, Ag, tile, T=T, beta=beta)
+    F, bt = Ag.cpu().numpy(), beta.cpu().numpy()
+    ref = orc.apply_qt(F, bt, B)  # the library's own reflectors: no condition number enters
+    M.apply_qt(P, Ag, T, Bg, tile)
+    tol = 64 * m * unit(P)
+    err = md_err(Bg.cpu().numpy(), ref)
+    print("  Q^T B %.2f u" % (err / unit(P)), flush=True)
+    assert err <= tol
+    M.apply_q(P, Ag, T, Bg, tile)
+    err = md_err(Bg.cpu().numpy(), B)
+    print("  Q Q^T B %.2f u" % (err / unit(P)), flush=True)
+    assert err <= 2 * tol
+    Tn = T.cpu().numpy()
+    for j in range(n):  # upper triangular, betas on the diagonal
+        assert np.all(Tn[:, j, j % tile + 1:] == 0.0)
+        assert np.array_equal(Tn[:, j, j % tile], bt[:, j])
