@@ -51,8 +51,11 @@ struct PanelArgs {
     long bps;
     double *T;  // panel T, W x W column-major (ld W), plane stride tps
     long tps;
-    double *gpart;  // [2][G][W*W + 2W][P] exchange slots between workgroups
+    double *gpart;  // [G][W*W][P] look-ahead sums of the workgroups
     unsigned *gbar; // barrier counter of this launch, zero on entry
+    unsigned long long *gtag;  // tagged words of the per-column exchange (tag_words), no word of them tagged
+                               // tag0 + 1 .. tag0 + wact on entry
+    unsigned tag0;  // column index of the panel's first column
     int *err;       // set to 1 if a barrier times out
     int G;          // workgroups in the launch
     unsigned spin;  // polls before a barrier gives up
@@ -90,6 +93,64 @@ __device__ inline void grid_sync(unsigned *ctr, unsigned target, int *err, unsig
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
+// The per-column exchange between the workgroups of a panel.  Each double goes out as two 8-byte
+// words, a 32-bit half beside the 32-bit number of the column, stored and loaded with relaxed
+// agent-scope atomics: a word that carries the number awaited is the word of that column, so the
+// data are their own flag and one round trip replaces the counter's release fence (a write-back of
+// the XCD's L2), arrival, polls and the loads after them.  Slots alternate with the column's parity:
+// a workgroup that publishes column j has read every workgroup's column j - 1, which those published
+// after they had read column j - 2.  Word w (limb w / 2, low half if w is odd) of column l from
+// workgroup b is at w G W + b W + l of its parity's half, the head row a_jl of workgroup 0 behind them.
+// n = 1024: dd panel 82 -> 71 us, qd 88 -> 75 us (16 and 8 columns) against the counter barrier.
+template <int P, int W>
+__host__ __device__ constexpr int tag_words(int G)  // both parities
+{
+    return 4 * P * W * (G + 1);
+}
+
+__device__ __forceinline__ void st_tagged(unsigned long long *p, long stride, double v, unsigned tag)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v), t = (unsigned long long)tag << 32;
+    __hip_atomic_store(p, t | (u >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p + stride, t | (u & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ double tagged_value(unsigned long long hi, unsigned long long lo)
+{
+    return __longlong_as_double((long long)((hi << 32) | (lo & 0xffffffffull)));
+}
+
+// One whole wave: loads the words of up to N items (item u of lane i at base + off[u] + w stride, u
+// taken where act[u]) until all of them carry the tag.  The polls are bounded, and once another
+// wait has given up every 256th poll gives up too; a time-out raises *err.
+template <int P, int N>
+__device__ __forceinline__ void poll_tagged(const unsigned long long *base, const long (&off)[N], const long (&stride)[N],
+                                            const bool (&act)[N], unsigned tag, unsigned long long (&wd)[N][2 * P],
+                                            int *err, unsigned spin)
+{
+    unsigned spins = 0;
+    for (;;) {
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int w = 0; w < 2 * P; ++w)
+                wd[u][w] = act[u] ? __hip_atomic_load(base + off[u] + w * stride[u], __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT)
+                                  : (unsigned long long)tag << 32;
+        bool ok = true;
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+            for (int w = 0; w < 2 * P; ++w) ok = ok && (unsigned)(wd[u][w] >> 32) == tag;
+        if (__all(ok)) break;
+        if ((spins & 255u) == 255u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
+        if (++spins > spin) {
+            __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            break;
+        }
+    }
 }
 
 // Sum over a workgroup of per-thread partials of WW pairs: thread t holds a partial of pair
@@ -222,7 +283,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
 {
     constexpr int S = NT / W;
     constexpr int NW = NT / 64;
-    constexpr int SLOT = (W * W + 2 * W) * P;  // doubles per workgroup exchange slot
+    constexpr int SLOT = W * W * P;  // doubles per workgroup of the look-ahead exchange
     static_assert(64 % W == 0 && S >= 2 * W && NW >= 4, "panel layout");
     __shared__ double s_part[NW * W * W * P];
     __shared__ double s_comb[NT * P];     // pair_sum partials
@@ -251,7 +312,6 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
     const int src0 = lane & ~(W - 1);
     const int off = g.off;
     const long hh = (long)g.h + off;
-    unsigned nbar = 0;
 
     // Off-chain pieces of the compact-WY factor (block 0; beta and T are written by it only).
     // beta_jj = 1 - x1/mu, or -(1/mu)/rho where that form cancels (wave 2)
@@ -359,15 +419,15 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
         }
         if (g.G > 1) {
             if (wid == 0) {
-                double *mine = g.gpart + (size_t)((nbar & 1) * g.G + bid) * SLOT;
+                double *mine = g.gpart + (size_t)bid * SLOT;
                 for (int q = lane; q < WW; q += 64) {
 #pragma unroll
                     for (int k = 0; k < P; ++k) st_coherent(mine + q * P + k, s_gram[q * P + k]);
                 }
-                grid_sync(g.gbar, (nbar + 1) * (unsigned)g.G, g.err, g.spin);
+                grid_sync(g.gbar, (unsigned)g.G, g.err, g.spin);
             }
             __syncthreads();
-            const double *base = g.gpart + (size_t)((nbar & 1) * g.G) * SLOT;
+            const double *base = g.gpart;
             // the workgroups' slots are loaded in batches of NB before they are added (same
             // order), so a batch costs one round trip
             constexpr int NB = (P >= 8) ? 1 : 8;
@@ -387,7 +447,6 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
             }
             pair_sum<P, WW, NT, false>(t, s_comb, s_gram);
         }
-        ++nbar;
         // -U(i, cc) = -sum_{l<=i} T'(l, i) S(l, cc) into s_hrow (scratch); the K threads of a
         // pair split the sum over l
         {
@@ -465,37 +524,49 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
             for (int m = W; m < (NW * W < 64 ? NW * W : 64); m <<= 1) acc_add_acc(ta, shfl_xor_acc(ta, m));
             V<P> hd = (bid == 0) ? lds_ld<P>(&s_head[(lane % W) * P]) : zero<P>();
             if (g.G > 1) {
-                double *mine = g.gpart + (size_t)((nbar & 1) * g.G + bid) * SLOT;
+                const unsigned tag = g.tag0 + (unsigned)j + 1u;
+                const long GW = (long)g.G * W;
+                unsigned long long *base = g.gtag + (long)(j & 1) * 2 * P * (GW + W);
                 if (lane < W) {
 #pragma unroll
-                    for (int k = 0; k < P; ++k) st_coherent(mine + lane * P + k, ta.s[k]);
+                    for (int k = 0; k < P; ++k) st_tagged(base + 2 * k * GW + (long)bid * W + lane, GW, ta.s[k], tag);
                     if (bid == 0) {
 #pragma unroll
-                        for (int k = 0; k < P; ++k) st_coherent(mine + (W + lane) * P + k, hd.x[k]);
+                        for (int k = 0; k < P; ++k) st_tagged(base + 2 * P * GW + 2 * k * W + lane, W, hd.x[k], tag);
                     }
                 }
-                grid_sync(g.gbar, (nbar + 1) * (unsigned)g.G, g.err, g.spin);
-                const double *base = g.gpart + (size_t)((nbar & 1) * g.G) * SLOT;
-                // all loads of a batch are issued before the first sum needs them (one round
-                // trip per batch instead of one per term; od, with one term per lane, keeps
-                // its registers); the summation order is unchanged
-                constexpr int NB = (P >= 8) ? 1 : 4;
-#pragma unroll
-                for (int k = 0; k < P; ++k) hd.x[k] = ld_coherent(base + (W + lane % W) * P + k);
+                // NB items (workgroup, column) a lane in flight at once, and the head row beside the
+                // first of them; the summation order is by item
+                constexpr int NB = (P >= 8) ? 2 : 4;
                 ta = acc_zero<P>();
                 const int tot = g.G * W;
-                for (int i0 = lane; i0 < tot; i0 += NB * 64) {
-                    Acc<P> o[NB];
+                for (int i0 = lane, first = 1; i0 - lane < tot; i0 += NB * 64, first = 0) {
+                    unsigned long long wd[NB + 1][2 * P];
+                    long offs[NB + 1], strd[NB + 1];
+                    bool act[NB + 1];
 #pragma unroll
                     for (int u = 0; u < NB; ++u) {
-                        const int i = i0 + u * 64;
-                        const double *q = base + (size_t)(i / W) * SLOT + (i % W) * P;
+                        offs[u] = i0 + u * 64;
+                        strd[u] = GW;
+                        act[u] = i0 + u * 64 < tot;
+                    }
+                    offs[NB] = 2 * P * GW + lane % W;
+                    strd[NB] = W;
+                    act[NB] = first != 0;
+                    poll_tagged<P, NB + 1>(base, offs, strd, act, tag, wd, g.err, g.spin);
+                    if (first) {
 #pragma unroll
-                        for (int k = 0; k < P; ++k) o[u].s[k] = (i < tot) ? ld_coherent(q + k) : 0.0;
+                        for (int k = 0; k < P; ++k) hd.x[k] = tagged_value(wd[NB][2 * k], wd[NB][2 * k + 1]);
                     }
 #pragma unroll
-                    for (int u = 0; u < NB; ++u)
-                        if (i0 + u * 64 < tot) acc_add_acc(ta, o[u]);
+                    for (int u = 0; u < NB; ++u) {
+                        if (act[u]) {
+                            Acc<P> o;
+#pragma unroll
+                            for (int k = 0; k < P; ++k) o.s[k] = tagged_value(wd[u][2 * k], wd[u][2 * k + 1]);
+                            acc_add_acc(ta, o);
+                        }
+                    }
                 }
                 const int lim = (g.G * W < 64) ? g.G * W : 64;
                 for (int m = W; m < lim; m <<= 1) acc_add_acc(ta, shfl_xor_acc(ta, m));
@@ -517,7 +588,6 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
                 if constexpr (kEarlyW) cx = t_w(j - 1, cx);  // in the shadow of the reduction
             }
         }
-        ++nbar;
         __syncthreads();  // B2
         // ---- 2. Householder scalars, identical in every lane and every workgroup
         const V<P> sig = lds_ld<P>(&s_tot[j * P]);
@@ -858,7 +928,7 @@ __global__ __launch_bounds__(kThreads) void k_apply_u(ApplyArgs g)
 // times (wall clock ticks) are recorded per problem.
 constexpr int kBatchRows = 512;
 constexpr int kTeamMax = 16;      // most workgroups on one problem
-constexpr int kTeamCtrs = 2 + kBatchRows / 4;  // team barrier + one counter per panel (W >= 4)
+constexpr int kTeamCtrs = 1;      // a team's barrier counter
 
 struct BatchDesc {
     int m, n;
@@ -875,7 +945,7 @@ struct BatchArgs {
     double *scratch;    // per workgroup: beta (kBatchRows*P)
     unsigned *counter;  // zero on entry
     unsigned *tctr;     // per problem: kTeamCtrs barrier counters, zero on entry
-    double *xch;        // per problem: T (W^2 P) and panel_run's exchange slots (2 kTeamMax (W^2 + 2W) P)
+    double *xch;        // per problem: T (W^2 P) and panel_run's exchange words (2 kTeamMax (W^2 + 2W) P doubles)
     int *err;           // set if a team barrier times out
     unsigned spin;      // polls before a team barrier gives up
     int *info;          // per problem
@@ -979,6 +1049,7 @@ __global__ __launch_bounds__(NT) void k_batch(BatchArgs g)
     constexpr int NW = NT / 64;
     constexpr long WWP = (long)W * W * P;
     constexpr long XCHP = WWP + 2L * kTeamMax * (W * W + 2 * W) * P;
+    static_assert(tag_words<P, W>(kTeamMax) <= 2 * kTeamMax * (W * W + 2 * W) * P, "k_batch: exchange area");
     constexpr bool STAGED = W * P <= 16;  // the panel's Y staged in LDS (at most 64 KiB)
     __shared__ double sY[STAGED ? W * P * kBatchRows : 1];
     __shared__ double s_y[kBatchRows * P];
@@ -1012,6 +1083,13 @@ __global__ __launch_bounds__(NT) void k_batch(BatchArgs g)
         double *bp = g.b + d.b_off;
         double *pxch = g.xch + (long)d.idx * XCHP;
         const long lda = d.m, ps = (long)d.m * d.n;
+        // the exchange words of an earlier problem or batch carry the same column numbers
+        unsigned long long *gtag = (unsigned long long *)(pxch + WWP);
+        if (team > 1) {
+            for (int e = mem * NT + threadIdx.x; e < tag_words<P, W>(team); e += team * NT)
+                __hip_atomic_store(gtag + e, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            team_sync();
+        }
         for (int c0 = 0; c0 < d.n; c0 += W) {
             PanelArgs pa;
             pa.A = A + (long)c0 * lda + c0;
@@ -1026,8 +1104,10 @@ __global__ __launch_bounds__(NT) void k_batch(BatchArgs g)
             pa.bps = kBatchRows;
             pa.T = pxch;  // written by member 0, read by every member after the team barrier
             pa.tps = (long)W * W;
-            pa.gpart = pxch + WWP;
-            pa.gbar = ctr + 1 + c0 / W;
+            pa.gpart = nullptr;  // no look-ahead (off = 0)
+            pa.gbar = nullptr;
+            pa.gtag = gtag;
+            pa.tag0 = (unsigned)c0;
             pa.err = g.err;
             pa.G = team;
             pa.spin = g.spin;
@@ -1221,6 +1301,15 @@ __global__ void k_zero_u32(unsigned *p, int n)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
+}
+
+// before a factorisation: barrier counters (ctr, n of them), the time-out flag and the exchange words
+__global__ void k_zero_sync(unsigned *ctr, int n, int *err, unsigned long long *tags, int ntag)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    for (int k = i; k < n; k += gridDim.x * blockDim.x) ctr[k] = 0u;
+    if (i < 4) err[i] = 0;
+    if (i < ntag) tags[i] = 0ull;
 }
 
 __global__ void k_copy(const double *src, long sps, double *dst, long dps, int n, int P)
@@ -2226,8 +2315,12 @@ int qr_panels(const Ctx<P> &cx, int m, int n, double *A, long lda, long psa, dou
     const int rows_per_wg = cf.nt / W * cf.r;
     const int nleaves = cx.L.nleaves;
     const Tuning tu = tuning();
-    MDLS_LAUNCH("k_zero", P, 0, k_zero_u32, dim3((nleaves + 1 + 255) / 256), dim3(256), cx.s, cx.ctr(), nleaves + 1);
-    MDLS_LAUNCH("k_zero", P, 0, k_zero_u32, dim3(1), dim3(256), cx.s, (unsigned *)cx.err(), 4);
+    // the exchange words behind the look-ahead sums of kGMax workgroups
+    static_assert(kGMax * W * W * P + tag_words<P, W>(kGMax) <= 2 * kGMax * (W * W + 2 * W) * P, "exchange area");
+    unsigned long long *gtag = (unsigned long long *)(cx.gpart() + (size_t)kGMax * W * W * P);
+    const int ntag = tag_words<P, W>(panel_groups(P, m));
+    MDLS_LAUNCH("k_zero", P, 0, k_zero_sync, dim3((ntag + 255) / 256), dim3(256), cx.s, cx.ctr(), nleaves + 1, cx.err(),
+                gtag, ntag);
     const long tps = (long)W * W * nleaves;
     SideStream *ss = (nleaves > 1 && tu.lookahead) ? side_stream() : nullptr;
     for (int l = 0; l < nleaves; ++l) {
@@ -2250,6 +2343,8 @@ int qr_panels(const Ctx<P> &cx, int m, int n, double *A, long lda, long psa, dou
         pa.tps = tps;
         pa.gpart = cx.gpart();
         pa.gbar = cx.ctr() + l;
+        pa.gtag = gtag;
+        pa.tag0 = (unsigned)c0;
         pa.err = cx.err();
         pa.spin = tu.spin_limit;
         int G = (h + off + rows_per_wg - 1) / rows_per_wg;
