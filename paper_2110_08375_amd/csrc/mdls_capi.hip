@@ -79,6 +79,8 @@ std::atomic<int> g_cpanel{2};
 
 // occupancy-derived capacity of the panel kernel, per (device, precision index, variant)
 std::atomic<int> g_capacity[kMaxDev][4][2];
+// the step kernel's, per (device, precision index)
+std::atomic<int> g_step_capacity[kMaxDev][4];
 
 int pidx(int P) { return P == 1 ? 0 : P == 2 ? 1 : P == 4 ? 2 : 3; }
 
@@ -135,6 +137,20 @@ int panel_capacity(int P, int m)
     default: per_cu = panel_occupancy_t<8>(cf); break;
     }
     c = per_cu * cus;
+    if (c > 0) slot.store(c, std::memory_order_relaxed);
+    return c;
+}
+
+int step_capacity(int P)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDev) return 0;
+    std::atomic<int> &slot = g_step_capacity[dev][pidx(P)];
+    int c = slot.load(std::memory_order_relaxed);
+    if (c > 0) return c;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) return 0;
+    c = cus * (P == 1 ? step_occupancy_t<1>() : P == 2 ? step_occupancy_t<2>() : step_occupancy_t<4>());
     if (c > 0) slot.store(c, std::memory_order_relaxed);
     return c;
 }

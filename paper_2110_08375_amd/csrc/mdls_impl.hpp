@@ -263,8 +263,10 @@ __device__ __forceinline__ int slot_scatter_index(int lane)
 //
 // When off = W the kernel first applies the previous panel's block reflector to its own
 // columns, C := C - Y' T'^T (Y'^T C) over the rows from the previous diagonal down (this is
-// the look-ahead: the rest of the trailing matrix is updated by the k_apply_s/t/u kernels
-// concurrently).
+// the look-ahead: the rest of the trailing matrix is updated concurrently, by other workgroups
+// of the launch or by the k_apply_s/t/u kernels).  The workgroup's rows of Y' (sy: R W P S doubles
+// of LDS) and T' are staged once, one element a thread and row: the W threads of a row then read
+// them from LDS, in place of W loads each from a block that other XCDs have just written.
 //
 // Column j of the panel, x = A(j:h, j) with x1 = a_jj, sigma = sum_{i>j} x_i^2, q = x1^2 + sigma,
 // mu = sqrt(q): the Householder vector of Golub-Van Loan 5.1.1 is v = x rho below the
@@ -278,29 +280,38 @@ __device__ __forceinline__ int slot_scatter_index(int lane)
 // cancel (sigma < x1^2: mu + x1 for x1 < 0, 1 - x1/mu for x1 > 0) rho = -1/(mu - x1) and
 // beta = -(1/mu)/rho are used instead.  Column j of T follows from
 // T(0:j, j) = -beta_j T(0:j, 0:j) (Y(:, 0:j)^T v_j) (Schreiber and Van Loan's compact WY).
+template <int P, int W, int NT>
+struct PanelLds {
+    double part[NT / 64 * W * W * P];
+    double comb[NT * P];     // pair_sum partials
+    double head[W * P];
+    double tot[W * P];       // column j's reduction: sigma (l = j), d_l, Gram sums
+    double hd[W * P];        // row j: a_jl
+    double mu[P];
+    double iq[P];            // 1/q
+    double is[P];            // 1/sigma
+    double fc[W * W * P];    // [j][c]: w_c = v_j^T a_c (deferred row-j update)
+    double info[W * 2 * P];  // per column: 1/mu, x1
+    double gram[W * W * P];  // [j][l]: sum_{i>j} x_j(i) x_l(i), l < j
+    double hrow[W * W * P];  // [j][l]: a_jl when column j is processed, l < j
+    double rho[W * P];
+    double beta[W * P];
+    double T[W * W * P];     // T, column-major
+    int flag[W];             // per column: 1 sigma == 0, 2 beta from rho (x1 > 0, sigma < x1^2)
+};
+
 template <int P, int W, int R, int NT>
-__device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
+__device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<P, W, NT> &lds, double *sy)
 {
     constexpr int S = NT / W;
     constexpr int NW = NT / 64;
     constexpr int SLOT = W * W * P;  // doubles per workgroup of the look-ahead exchange
     static_assert(64 % W == 0 && S >= 2 * W && NW >= 4, "panel layout");
-    __shared__ double s_part[NW * W * W * P];
-    __shared__ double s_comb[NT * P];     // pair_sum partials
-    __shared__ double s_head[W * P];
-    __shared__ double s_tot[W * P];       // column j's reduction: sigma (l = j), d_l, Gram sums
-    __shared__ double s_hd[W * P];        // row j: a_jl
-    __shared__ double s_mu[P];
-    __shared__ double s_iq[P];            // 1/q
-    __shared__ double s_is[P];            // 1/sigma
-    __shared__ double s_fc[W * W * P];    // [j][c]: w_c = v_j^T a_c (deferred row-j update)
-    __shared__ double s_info[W * 2 * P];  // per column: 1/mu, x1
-    __shared__ double s_gram[W * W * P];  // [j][l]: sum_{i>j} x_j(i) x_l(i), l < j
-    __shared__ double s_hrow[W * W * P];  // [j][l]: a_jl when column j is processed, l < j
-    __shared__ double s_rho[W * P];
-    __shared__ double s_beta[W * P];
-    __shared__ double s_T[W * W * P];     // T, column-major
-    __shared__ int s_flag[W];             // per column: 1 sigma == 0, 2 beta from rho (x1 > 0, sigma < x1^2)
+    double *const s_part = lds.part, *const s_comb = lds.comb, *const s_head = lds.head, *const s_tot = lds.tot;
+    double *const s_hd = lds.hd, *const s_mu = lds.mu, *const s_iq = lds.iq, *const s_is = lds.is;
+    double *const s_fc = lds.fc, *const s_info = lds.info, *const s_gram = lds.gram, *const s_hrow = lds.hrow;
+    double *const s_rho = lds.rho, *const s_beta = lds.beta, *const s_T = lds.T;
+    int *const s_flag = lds.flag;
 
     // The panel is the critical path of the factorisation: its waves take issue priority over
     // the trailing-update waves that may share their compute unit.
@@ -375,6 +386,26 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
         const long r = rbase + k * rstride;
         a[k] = (r < hh && c < g.wact) ? ldm<P>(g.A, g.ps, c * g.lda + r) : zero<P>();
     }
+    auto ysl = [&](int k, int i) __attribute__((always_inline)) {
+        V<P> y;
+#pragma unroll
+        for (int e = 0; e < P; ++e) y.x[e] = sy[((k * W + i) * P + e) * S + slot];
+        return y;
+    };
+    if (off) {
+        const int row = tid % S, i = tid / S;
+        V<P> yv[R], tv = zero<P>();
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+            yv[k] = y_entry<P>(g.Yp, g.lda, g.ps, (long)bid * S + row + k * rstride, i, (int)hh, W);
+        if (tid < W * W) tv = ldm<P>(g.Tp, g.tps, tid);
+#pragma unroll
+        for (int k = 0; k < R; ++k)
+#pragma unroll
+            for (int e = 0; e < P; ++e) sy[((k * W + i) * P + e) * S + row] = yv[k].x[e];
+        if (tid < W * W) lds_st(&s_T[tid * P], tv);  // T', until the first column of T is formed
+        __syncthreads();
+    }
 
     // ---- 0. apply the previous panel's reflectors to this panel (look-ahead update):
     //         S = Y'^T C (W x W), -U = -T'^T S, C += Y' (-U)
@@ -388,7 +419,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
             if (r < hh) {
 #pragma unroll
                 for (int i = 0; i < W; ++i)
-                    acc_fma_step(sacc[i], y_entry<P>(g.Yp, g.lda, g.ps, r, i, (int)hh, W), a[k], k);
+                    acc_fma_step(sacc[i], ysl(k, i), a[k], k);
             }
         }
         // sum over the wave's row slots; lane (.., c) ends with NF accumulators of column c
@@ -453,7 +484,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
             const int i = pq / W, cc = pq % W;
             Acc<P> u = acc_zero<P>();
             for (int l = psub; l <= i; l += K)
-                acc_fma(u, ldm<P>(g.Tp, g.tps, (long)i * W + l), lds_ld<P>(&s_gram[(l * W + cc) * P]));
+                acc_fma(u, lds_ld<P>(&s_T[(i * W + l) * P]), lds_ld<P>(&s_gram[(l * W + cc) * P]));
             pair_sum<P, WW, NT, true>(u, s_comb, s_hrow);
         }
         // even and odd i in two accumulators, so the two halves of the sum overlap
@@ -464,9 +495,8 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
                 Acc<P> t0 = acc_from(a[k]), t1 = acc_zero<P>();
 #pragma unroll
                 for (int i = 0; i < W; i += 2) {
-                    acc_fma(t0, y_entry<P>(g.Yp, g.lda, g.ps, r, i, (int)hh, W), lds_ld<P>(&s_hrow[(i * W + c) * P]));
-                    acc_fma(t1, y_entry<P>(g.Yp, g.lda, g.ps, r, i + 1, (int)hh, W),
-                            lds_ld<P>(&s_hrow[((i + 1) * W + c) * P]));
+                    acc_fma(t0, ysl(k, i), lds_ld<P>(&s_hrow[(i * W + c) * P]));
+                    acc_fma(t1, ysl(k, i + 1), lds_ld<P>(&s_hrow[((i + 1) * W + c) * P]));
                 }
                 acc_add_acc(t0, t1);
                 a[k] = acc_get(t0);
@@ -685,7 +715,9 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid)
 template <int P, int W, int R, int NT>
 __global__ __launch_bounds__(NT) void k_panel(PanelArgs g)
 {
-    panel_run<P, W, R, NT>(g, blockIdx.x);
+    __shared__ PanelLds<P, W, NT> lds;
+    __shared__ double sy[R * P * NT];  // R W P S doubles
+    panel_run<P, W, R, NT>(g, blockIdx.x, lds, sy);
 }
 
 // ============================================================================ trailing update
@@ -721,6 +753,7 @@ struct ApplyArgs {
     int rb, nrb;   // rows per unit (a multiple of 64, at most rb_max) and row blocks
     double *part;  // [ncol][nrb][W][P] partial sums
     double *nu;    // [ncol][W][P] -U
+    int rs;        // update_run: waves per column, 1 or 2
 };
 
 // Column gc of this launch (null past the end); its plane stride in *cps.
@@ -916,6 +949,234 @@ __global__ __launch_bounds__(kThreads) void k_apply_u(ApplyArgs g)
     }
 }
 
+// ============================================================================ factorisation step
+// One launch per panel l: workgroups 0 .. G - 1 factor panel l (panel_run, which first applies panel
+// l - 1 to its own columns) and the others apply panel l - 1 to the columns right of panel l and to B,
+// C := C - Y T^T (Y^T C), whole columns at a time: a wave (or two, half the rows each) forms Y^T c over all
+// rows, U = T^T (Y^T c) lane parallel, then c -= Y U, with Y passing through LDS in chunks of kStepRows rows
+// for the workgroup's columns (the next chunk's loads in flight).  The panel is a latency chain on few
+// workgroups, so the update costs nothing while its columns find compute units of their own.  Against
+// a side stream for the update (three kernels, and events in front of every panel) this saves the event
+// wait, about 11 us a panel, the launches (host time of a dd n = 1024 solve 3.3 -> 0.25 ms) and the update's
+// partial sums: dd n = 1024 5.85 -> 4.86 ms, qd 13.0 -> 12.1, dd 128 x 128 0.67 -> 0.54, refined od
+// n = 2048 23.1 -> 17.4.  The panel's workgroups come first in the grid and no other workgroup waits for
+// anything, so all of them become resident.  The update is bound by the FP64 issue rate: qd, 1008
+// columns of 1024 rows, 94 us alone, 81 % of the issue slots of its waves' life time.
+constexpr int kStepRows = 128;  // rows of Y staged at once, twice
+
+struct StepArgs {
+    PanelArgs p;   // p.G workgroups, 0 for the launch after the last panel
+    ApplyArgs a;   // the previous panel's update (a.ncol columns, 0 before the first)
+};
+
+// Plane k of a column block at a 32-bit byte offset: base and plane in scalar registers, so a lane's
+// addresses cost one register (64-bit addresses of every limb and column, kept across the loops, spilled,
+// and their reloads waited for the loads in flight: qd 200 us a launch in place of 75).
+template <int P>
+__device__ __forceinline__ V<P> ldm32(const double *X, long ps, unsigned boff)
+{
+    V<P> v;
+#pragma unroll
+    for (int k = 0; k < P; ++k) v.x[k] = *(const double *)((const char *)(X + k * ps) + boff);
+    return v;
+}
+
+template <int P, int W, int NT>
+struct UpdateLds {
+    double y[2][W * P * kStepRows];  // chunks of Y: limb k of column i at (i P + k) kStepRows + row
+    double s[NT / 64][W * P];        // a wave's S, for the wave that shares its column
+    double u[NT / 64][W * P];        // a wave's -U
+};
+
+template <int P, int W, int NT>
+__device__ __forceinline__ void update_run(const ApplyArgs &g, int u, int nu, UpdateLds<P, W, NT> &lds)
+{
+    constexpr int NW = NT / 64, RC = kStepRows, RL = RC / 64, EPT = W * RC / NT;
+    constexpr int LPI = 64 / W, NQ = (W * W + 63) / 64;
+    // columns of Y loaded from LDS ahead of their multiply-adds: as many instructions as an LDS read
+    // takes to come back (dd 48, qd 224); the barrier keeps the scheduler from pulling more of them
+    // forward, which spills
+    constexpr int GC = P <= 2 ? 4 : 2, NG = W / GC;
+    static_assert(W * RC % NT == 0 && NT % RC == 0 && RL == 2 && NG >= 2, "update_run layout");
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = (g.rs == 2) ? (wid & 1) : -1;  // the rows this wave takes of a chunk; -1: all
+    const int wcol = (g.rs == 2) ? (wid >> 1) : wid, ncw = NW / g.rs;
+    const int er = tid % RC, ei = tid / RC;  // this thread stages Y(er, ei + q NT / RC) of a chunk
+    const int nch = (g.h + RC - 1) / RC;
+    V<P> ys[EPT], cs[RL];
+    // loads from clamped places in bounds; stage() puts the zeros and the unit diagonal in
+    auto fetch_y = [&](int ch) __attribute__((always_inline)) {
+        const unsigned r = min(ch * RC + er, g.h - 1);
+#pragma unroll
+        for (int q = 0; q < EPT; ++q) {
+            const unsigned i = min(ei + q * (NT / RC), g.wact - 1);
+            ys[q] = ldm32<P>(g.Y, g.psy, (i * (unsigned)g.ldy + r) * 8u);
+        }
+    };
+    auto stage = [&](int ch) __attribute__((always_inline)) {
+        double *sY = lds.y[ch & 1];
+        const int r = ch * RC + er;
+#pragma unroll
+        for (int q = 0; q < EPT; ++q) {
+            const int i = ei + q * (NT / RC);
+            const bool in = i < g.wact && r < g.h;
+            const double one = (in && r == i) ? 1.0 : 0.0;
+#pragma unroll
+            for (int k = 0; k < P; ++k) sY[(i * P + k) * RC + er] = (in && r > i) ? ys[q].x[k] : (k == 0 ? one : 0.0);
+        }
+    };
+    // columns GC grp .. GC grp + GC - 1 of Y at row q 64 + lane of a chunk
+    auto load_y = [&](const double *sY, int q, int grp, V<P> (&y)[GC]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < GC; ++i)
+#pragma unroll
+            for (int k = 0; k < P; ++k) y[i].x[k] = sY[((grp * GC + i) * P + k) * RC + q * 64 + lane];
+    };
+#pragma unroll 1
+    for (int cg = u; cg * ncw < g.ncol; cg += nu) {
+        long cps = 0;
+        double *col = apply_col(g, cg * ncw + wcol, &cps);  // null past the end: the wave only stages
+        auto fetch_c = [&](int ch) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < RL; ++q)
+                if (col && q != 1 - half) cs[q] = ldm32<P>(col, cps, (unsigned)min(ch * RC + q * 64 + lane, g.h - 1) * 8u);
+        };
+        // ---- S = Y^T c
+        Acc<P> s[W];
+#pragma unroll
+        for (int i = 0; i < W; ++i) s[i] = acc_zero<P>();
+        int nt = 0;
+        __syncthreads();  // the last column group's readers
+        fetch_y(0);
+        fetch_c(0);
+        stage(0);
+        __syncthreads();
+#pragma unroll 1
+        for (int ch = 0; ch < nch; ++ch) {
+            const double *sY = lds.y[ch & 1];
+            V<P> cv[RL];
+#pragma unroll
+            for (int q = 0; q < RL; ++q) cv[q] = cs[q];
+            if (ch + 1 < nch) {
+                fetch_y(ch + 1);
+                fetch_c(ch + 1);
+            }
+#pragma unroll
+            for (int q = 0; q < RL; ++q) {
+                if (!col || q == 1 - half) continue;  // uniform
+                V<P> y[2][GC];
+                load_y(sY, q, 0, y[0]);
+#pragma unroll
+                for (int grp = 0; grp < NG; ++grp) {
+                    if (grp + 1 < NG) load_y(sY, q, grp + 1, y[(grp + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < GC; ++i) acc_fma(s[grp * GC + i], y[grp & 1][i], cv[q]);
+                }
+                if (++nt % kLazy<P> == 0) {
+#pragma unroll
+                    for (int i = 0; i < W; ++i) {
+                        s[i] = acc_from(acc_get(s[i]));
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+            }
+            if (ch + 1 < nch) stage(ch + 1);
+            __syncthreads();
+        }
+        reduce_scatter<P, W>(s, lane);  // lane q: S_(q / LPI)
+        if (g.rs == 2) {                // the two waves' sums, in the same order in both
+            if (lane % LPI == 0) {
+#pragma unroll
+                for (int k = 0; k < P; ++k) lds.s[wid][(lane / LPI) * P + k] = s[0].s[k];
+            }
+            __syncthreads();
+            V<P> o;
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                s[0].s[k] = lds.s[wid & ~1][(lane / LPI) * P + k];
+                o.x[k] = lds.s[wid | 1][(lane / LPI) * P + k];
+            }
+            acc_add(s[0], o);
+        }
+        // ---- U = T^T S: lane q = i W + l (+ 64 k) forms one product, the W lanes of an i are summed
+        const V<P> S = acc_get(s[0]);
+        const int l = lane % W;
+        const V<P> sl = shfl_md(S, l * LPI);
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) {
+            const int i = (lane + 64 * k) / W;
+            Acc<P> t = acc_zero<P>();
+            if (l <= i && i < g.wact) acc_fma(t, ldm32<P>(g.T, g.tps, (unsigned)(i * W + l) * 8u), sl);
+#pragma unroll
+            for (int m = 1; m < W; m <<= 1) acc_add_acc(t, shfl_xor_acc(t, m));
+            if (l == 0 && i < W) lds_st(&lds.u[wid][i * P], neg(acc_get(t)));
+        }
+        // ---- c -= Y U, the chunks from the last one back (it is still staged); even and odd columns of Y
+        // in two accumulators
+        V<P> nU[W];
+#pragma unroll
+        for (int i = 0; i < W; ++i) nU[i] = lds_ld<P>(&lds.u[wid][i * P]);
+        fetch_c(nch - 1);
+#pragma unroll 1
+        for (int ch = nch - 1; ch >= 0; --ch) {
+            const double *sY = lds.y[ch & 1];
+            V<P> cv[RL];
+#pragma unroll
+            for (int q = 0; q < RL; ++q) cv[q] = cs[q];
+            if (ch > 0) {
+                fetch_y(ch - 1);
+                fetch_c(ch - 1);
+            }
+#pragma unroll
+            for (int q = 0; q < RL; ++q) {
+                if (!col || q == 1 - half) continue;  // uniform
+                Acc<P> t0 = acc_from(cv[q]), t1 = acc_zero<P>();
+                V<P> y[2][GC];
+                load_y(sY, q, 0, y[0]);
+#pragma unroll
+                for (int grp = 0; grp < NG; ++grp) {
+                    if (grp + 1 < NG) load_y(sY, q, grp + 1, y[(grp + 1) & 1]);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < GC; i += 2) {
+                        acc_fma(t0, y[grp & 1][i], nU[grp * GC + i]);
+                        acc_fma(t1, y[grp & 1][i + 1], nU[grp * GC + i + 1]);
+                    }
+                }
+                acc_add_acc(t0, t1);
+                const int r = ch * RC + q * 64 + lane;
+                const V<P> v = acc_get(t0);
+                if (r < g.h) {
+#pragma unroll
+                    for (int k = 0; k < P; ++k) *(double *)((char *)(col + k * cps) + (unsigned)r * 8u) = v.x[k];
+                }
+            }
+            if (ch > 0) stage(ch - 1);
+            __syncthreads();
+        }
+    }
+}
+
+template <int P, int W, int R, int NT>
+__global__ __launch_bounds__(NT, 2) void k_step(StepArgs g)
+{
+    // one workgroup is either kind: the two layouts share the LDS
+    struct Panel {
+        PanelLds<P, W, NT> lds;
+        double sy[R * P * NT];
+    };
+    using Update = UpdateLds<P, W, NT>;
+    constexpr size_t bytes = sizeof(Panel) > sizeof(Update) ? sizeof(Panel) : sizeof(Update);
+    __shared__ double raw[bytes / sizeof(double)];
+    if ((int)blockIdx.x < g.p.G) {
+        Panel &l = *reinterpret_cast<Panel *>(raw);
+        panel_run<P, W, R, NT>(g.p, blockIdx.x, l.lds, l.sy);
+    } else {
+        update_run<P, W, NT>(g.a, blockIdx.x - g.p.G, gridDim.x - g.p.G, *reinterpret_cast<Update *>(raw));
+    }
+}
+
 // ============================================================================ batched solves
 // Many independent least-squares problems (m <= kBatchRows) in one persistent launch.  Each
 // workgroup takes the next slot from a counter; a slot names a problem and a member index.
@@ -1051,6 +1312,7 @@ __global__ __launch_bounds__(NT) void k_batch(BatchArgs g)
     constexpr long XCHP = WWP + 2L * kTeamMax * (W * W + 2 * W) * P;
     static_assert(tag_words<P, W>(kTeamMax) <= 2 * kTeamMax * (W * W + 2 * W) * P, "k_batch: exchange area");
     constexpr bool STAGED = W * P <= 16;  // the panel's Y staged in LDS (at most 64 KiB)
+    __shared__ PanelLds<P, W, NT> lds;
     __shared__ double sY[STAGED ? W * P * kBatchRows : 1];
     __shared__ double s_y[kBatchRows * P];
     __shared__ double s_r[kBatchRows * P];
@@ -1111,7 +1373,7 @@ __global__ __launch_bounds__(NT) void k_batch(BatchArgs g)
             pa.err = g.err;
             pa.G = team;
             pa.spin = g.spin;
-            panel_run<P, W, R, NT>(pa, mem);
+            panel_run<P, W, R, NT>(pa, mem, lds, nullptr);
             team_sync();
             if constexpr (STAGED) {
                 for (int e = threadIdx.x; e < W * pa.h; e += NT) {
@@ -2022,6 +2284,8 @@ int apply_grid_cap(int P, int h);
 // Workgroups of the panel kernel of precision P (current variant) that can be resident at once on
 // the current device (occupancy x compute units); 0 if the device cannot be queried.
 int panel_capacity(int P, int m);
+// The same of the step kernel of precision P (P <= 4).
+int step_capacity(int P);
 
 #define MDLS_LAUNCH(NAME, PREC, WORK, KERNEL, GRID, BLOCK, STREAM, ...)                       \
     do {                                                                                     \
@@ -2189,6 +2453,55 @@ void launch_panel(const PanelArgs &a, PanelCfg cf, hipStream_t s)
 #undef MDLS_PANEL_CASE
 }
 
+// The factorisation step kernel takes the default panel shape of P <= 4 up to this many rows.  A wave
+// of it updates whole columns, so beyond them the columns of a tall matrix, few and long, outlast the panel.
+template <int P>
+constexpr int step_rows()
+{
+    return P <= 2 ? 4096 : (P == 4 ? 2048 : 0);
+}
+
+constexpr long kStepLd = 1L << 24;  // the step kernel's byte offsets (16 columns of lda doubles) stay below 2^32
+
+template <int P>
+void launch_step(const StepArgs &a, int grid_cap, hipStream_t s)
+{
+    if constexpr (P <= 4) {
+        constexpr int W = Cfg<P>::W, NT = P <= 2 ? 512 : 256, R = P <= 2 ? 2 : 1, NW = NT / 64;
+        const PanelArgs &p = a.p;
+        const ApplyArgs &u = a.a;
+        double work = 0.0;
+        if (p.G > 0) {
+            work = p.off ? 2.0 * (p.h + p.off) * p.off * p.wact : 0.0;
+            for (int j = 0; j < p.wact; ++j) work += (p.h - j - 1) + 2.0 * (p.wact - j - 1) * (p.h - j);
+        }
+        if (u.ncol > 0) work += (2.0 * u.h * u.wact + 0.5 * u.wact * (u.wact + 1)) * u.ncol;
+        // two waves share a column of more than 1024 (dd) or 768 (qd) rows: alone a wave takes 67 us (dd)
+        // or 100 us (qd) for 1024 rows of it, and the panel beside it 77 or 88; below, one wave has
+        // half the staging (dd n = 1024: 4.86 ms against 4.93; qd n = 1024 with one wave throughout 12.5
+        // against 12.1)
+        StepArgs b = a;
+        b.a.rs = u.h > (P <= 2 ? 1024 : 768) ? 2 : 1;
+        const int ncw = NW / b.a.rs;
+        int nu = (u.ncol + ncw - 1) / ncw;
+        if (grid_cap > 0 && nu > grid_cap) nu = grid_cap;
+        if (p.G + nu > 0)
+            MDLS_LAUNCH("k_step", P, work, (k_step<P, W, R, NT>), dim3(p.G + nu), dim3(NT), s, b);
+    }
+}
+
+// Resident workgroups per CU of the step kernel (0 if the query fails).
+template <int P>
+int step_occupancy_t()
+{
+    int per_cu = 0;
+    if constexpr (P <= 4) {
+        constexpr int W = Cfg<P>::W, NT = P <= 2 ? 512 : 256, R = P <= 2 ? 2 : 1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_step<P, W, R, NT>, NT, 0) != hipSuccess) per_cu = 0;
+    }
+    return per_cu;
+}
+
 // Resident workgroups per CU of the panel kernel of shape cf (0 if the query fails).
 template <int P>
 int panel_occupancy_t(PanelCfg cf)
@@ -2300,10 +2613,12 @@ void launch_apply(const Ctx<P> &cx, ApplyArgs aa, int grid_cap, hipStream_t st)
 }
 
 // Householder QR of A (m x n) in narrow panels of W columns; B (nb columns, may be null)
-// receives Q^T B.  Panel l (l > 0) first applies panel l-1 to its own columns (k_panel with
-// off = W); apply(l) (k_apply_s, k_apply_t, k_apply_u) updates the columns from panel l+2 on,
-// and B.  With look-ahead (default; MDLS_LOOKAHEAD=0 turns it off) apply(l) runs on a side
-// stream concurrently with panel l+1:
+// receives Q^T B.  Panel l (l > 0) first applies panel l-1 to its own columns (off = W); apply(l) updates
+// the columns from panel l+2 on, and B.
+// Up to step_rows<P>() rows one k_step launch per panel does panel l and apply(l-1) side by side.
+// Otherwise (od, taller matrices, the alternative panel shape, the split-limb products) apply(l) is
+// k_apply_s, k_apply_t, k_apply_u, on a side stream concurrently with panel l+1 where mdls_init made
+// one:
 //   caller: panel(l) -> [wait apply(l-1)] -> panel(l+1) -> [wait apply(l)] -> panel(l+2) ...
 //   side:   [wait panel(l)] -> apply(l) -> [wait panel(l+1)] -> apply(l+1) ...
 // and its grid is capped so that CUs stay free for the panel's workgroups.
@@ -2322,18 +2637,16 @@ int qr_panels(const Ctx<P> &cx, int m, int n, double *A, long lda, long psa, dou
     MDLS_LAUNCH("k_zero", P, 0, k_zero_sync, dim3((ntag + 255) / 256), dim3(256), cx.s, cx.ctr(), nleaves + 1, cx.err(),
                 gtag, ntag);
     const long tps = (long)W * W * nleaves;
-    SideStream *ss = (nleaves > 1 && tu.lookahead) ? side_stream() : nullptr;
-    for (int l = 0; l < nleaves; ++l) {
+    // panel l's arguments
+    auto panel_args = [&](int l) {
         const int c0 = l * W;
-        const int wact = (n - c0 < W) ? (n - c0) : W;
-        const int h = m - c0;
         const int off = (l > 0) ? W : 0;
         PanelArgs pa;
         pa.A = A + (long)c0 * lda + (c0 - off);
         pa.lda = lda;
         pa.ps = psa;
-        pa.h = h;
-        pa.wact = wact;
+        pa.h = m - c0;
+        pa.wact = (n - c0 < W) ? (n - c0) : W;
         pa.off = off;
         pa.Yp = off ? A + (long)(c0 - W) * lda + (c0 - W) : nullptr;
         pa.Tp = off ? cx.leafT() + (long)(l - 1) * W * W : nullptr;
@@ -2347,23 +2660,23 @@ int qr_panels(const Ctx<P> &cx, int m, int n, double *A, long lda, long psa, dou
         pa.tag0 = (unsigned)c0;
         pa.err = cx.err();
         pa.spin = tu.spin_limit;
-        int G = (h + off + rows_per_wg - 1) / rows_per_wg;
-        if (G < 1) G = 1;
-        pa.G = G;
-        if (ss && l >= 2 && hipStreamWaitEvent(cx.s, ss->ev_wide[l & 1], 0) != hipSuccess)  // apply(l-2)
-            return MDLS_EHIP;
-        launch_panel<P, W>(pa, cf, cx.s);
-
-        // the update of everything right of the next panel, and of B
+        pa.G = (pa.h + off + rows_per_wg - 1) / rows_per_wg;
+        if (pa.G < 1) pa.G = 1;
+        return pa;
+    };
+    // panel l applied to the columns right of panel l + 1, and to B
+    auto apply_args = [&](int l) {
+        const int c0 = l * W;
+        const int wact = (n - c0 < W) ? (n - c0) : W;
         const int nc = n - c0 - wact;
-        const int nn = (nc < W) ? nc : W;  // the next panel's columns: updated by panel l+1 itself
-        ApplyArgs aa;
+        const int nn = (nc < W) ? nc : W;  // the next panel's columns: updated by panel l + 1 itself
+        ApplyArgs aa{};
         aa.Y = A + (long)c0 * lda + c0;
         aa.ldy = lda;
         aa.psy = psa;
-        aa.h = h;
+        aa.h = m - c0;
         aa.wact = wact;
-        aa.T = pa.T;
+        aa.T = cx.leafT() + (long)l * W * W;
         aa.tps = tps;
         aa.C = A + (long)(c0 + wact + nn) * lda + c0;
         aa.ldc = lda;
@@ -2373,11 +2686,34 @@ int qr_panels(const Ctx<P> &cx, int m, int n, double *A, long lda, long psa, dou
         aa.ldb = ldb;
         aa.psb = psb;
         aa.nb = B ? nb : 0;
+        return aa;
+    };
+    if (m <= step_rows<P>() && lda <= kStepLd && !tu.panel_variant && !cx.split &&
+        panel_groups(P, m) <= step_capacity(P)) {
+        for (int l = 0; l <= nleaves; ++l) {
+            StepArgs sa{};
+            if (l < nleaves) sa.p = panel_args(l);
+            if (l > 0) {
+                sa.a = apply_args(l - 1);
+                sa.a.ncol = sa.a.nc + sa.a.nb;
+            }
+            launch_step<P>(sa, tu.apply_grid_cap, cx.s);
+        }
+        return 0;
+    }
+    SideStream *ss = (nleaves > 1 && tu.lookahead) ? side_stream() : nullptr;
+    for (int l = 0; l < nleaves; ++l) {
+        const PanelArgs pa = panel_args(l);
+        if (ss && l >= 2 && hipStreamWaitEvent(cx.s, ss->ev_wide[l & 1], 0) != hipSuccess)  // apply(l-2)
+            return MDLS_EHIP;
+        launch_panel<P, W>(pa, cf, cx.s);
+
+        const ApplyArgs aa = apply_args(l);
         if (ss) {
             if (hipEventRecord(ss->ev_panel, cx.s) != hipSuccess ||
                 hipStreamWaitEvent(ss->q, ss->ev_panel, 0) != hipSuccess)
                 return MDLS_EHIP;
-            launch_apply<P>(cx, aa, apply_grid_cap(P, h), ss->q);
+            launch_apply<P>(cx, aa, apply_grid_cap(P, aa.h), ss->q);
             if (hipEventRecord(ss->ev_wide[l & 1], ss->q) != hipSuccess) return MDLS_EHIP;
         } else {
             launch_apply<P>(cx, aa, 0, cx.s);
@@ -2988,6 +3324,7 @@ int refine_t(int m, int n, int tile, const double *A, int lda, const double *b, 
                                 void *, hipStream_t);                                                          \
     X template int form_q_t<P>(int, int, int, const double *, int, const double *, int, double *, int, int,     \
                                void *, hipStream_t);                                                          \
-    X template int panel_occupancy_t<P>(PanelCfg);
+    X template int panel_occupancy_t<P>(PanelCfg);                                                         \
+    X template int step_occupancy_t<P>();
 
 }  // namespace mdls_impl
