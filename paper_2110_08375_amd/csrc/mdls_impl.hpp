@@ -285,7 +285,7 @@ struct PanelLds {
     double part[NT / 64 * W * W * P];
     double comb[NT * P];     // pair_sum partials
     double head[W * P];
-    double tot[W * P];       // column j's reduction: sigma (l = j), d_l, Gram sums
+    double psum[NT / 128 * W * P];  // column j's reduction by poll wave: sigma (l = j), d_l, Gram sums
     double hd[W * P];        // row j: a_jl
     double mu[P];
     double iq[P];            // 1/q
@@ -305,9 +305,10 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
 {
     constexpr int S = NT / W;
     constexpr int NW = NT / 64;
+    constexpr int NPW = NW / 2;      // waves that collect the workgroups' sums
     constexpr int SLOT = W * W * P;  // doubles per workgroup of the look-ahead exchange
     static_assert(64 % W == 0 && S >= 2 * W && NW >= 4, "panel layout");
-    double *const s_part = lds.part, *const s_comb = lds.comb, *const s_head = lds.head, *const s_tot = lds.tot;
+    double *const s_part = lds.part, *const s_comb = lds.comb, *const s_head = lds.head, *const s_psum = lds.psum;
     double *const s_hd = lds.hd, *const s_mu = lds.mu, *const s_iq = lds.iq, *const s_is = lds.is;
     double *const s_fc = lds.fc, *const s_info = lds.info, *const s_gram = lds.gram, *const s_hrow = lds.hrow;
     double *const s_rho = lds.rho, *const s_beta = lds.beta, *const s_T = lds.T;
@@ -325,7 +326,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
     const long hh = (long)g.h + off;
 
     // Off-chain pieces of the compact-WY factor (block 0; beta and T are written by it only).
-    // beta_jj = 1 - x1/mu, or -(1/mu)/rho where that form cancels (wave 2)
+    // beta_jj = 1 - x1/mu, or -(1/mu)/rho where that form cancels
     auto t_beta = [&](int jj) __attribute__((always_inline)) {
         V<P> beta = zero<P>();
         if (!(s_flag[jj] & 1)) {
@@ -340,7 +341,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
             stm(g.beta, g.bps, jj, beta);
         }
     };
-    // lane l < jj: g(l, jj) = y_l^T v_jj = rho_l (a_jj,l + rho_jj gsum_jj,l) (wave 3)
+    // lane l < jj: g(l, jj) = y_l^T v_jj = rho_l (a_jj,l + rho_jj gsum_jj,l)
     auto t_g = [&](int jj) __attribute__((always_inline)) {
         V<P> gv = zero<P>();
         if (lane < jj) {
@@ -349,7 +350,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
         }
         return gv;
     };
-    // lane l < jj: w_l = sum_{l <= k < jj} T(l, k) g(k, jj) (wave 3); even and odd k in two
+    // lane l < jj: w_l = sum_{l <= k < jj} T(l, k) g(k, jj); even and odd k in two
     // accumulators, so the two halves of the sum overlap
     auto t_w = [&](int jj, const V<P> &gv) __attribute__((always_inline)) {
         Acc<P> w0 = acc_zero<P>(), w1 = acc_zero<P>();
@@ -368,7 +369,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
         acc_add_acc(w0, w1);
         return acc_get(w0);
     };
-    // T(0:jj, jj) = -beta_jj w, T(jj, jj) = beta_jj, zero below (wave 3)
+    // T(0:jj, jj) = -beta_jj w, T(jj, jj) = beta_jj, zero below
     auto t_store = [&](int jj, const V<P> &w) __attribute__((always_inline)) {
         const V<P> bj = lds_ld<P>(&s_beta[jj * P]);
         if (lane < W) {
@@ -505,22 +506,28 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
         __syncthreads();
     }
 
-    // Per column j the serial chain (reduction, mu, 1/mu, w_c) runs through waves 0 and 1; the
-    // other waves do the off-chain work between the same workgroup barriers:
-    //   [B1, B2]  wave 0: reduction of the partial sums (and the grid exchange);
-    //             wave 2: beta of column j-1; wave 3: g(l, j-1) (block 0 only), and for
-    //             P <= 4 also w = T(:, :j-1) g(:, j-1), which is longer than mu there
-    //   [B2, M]   wave 0: mu = sqrt(q); wave 1: 1/q; wave 2: 1/sigma; wave 3 (P = 8): w
+    // Per column j the serial chain (reduction, mu, 1/mu, w_c) runs between workgroup barriers, the
+    // off-chain work in other waves beside it:
+    //   [B1, B2]  wave 0: sum of the partial sums, published; waves 0 .. NPW - 1: the workgroups' sums,
+    //             each wave its share of them (one or two items a lane in flight, so that a poll is short);
+    //             in block 0 wave NW - 2: beta of column j-1, wave NW - 1: g(l, j-1) and for P <= 4 also
+    //             w = T(:, :j-1) g(:, j-1), which is longer than mu there
+    //   after B2  every wave adds the NPW sums of its own column
+    //   [B2, M]   wave 0: mu = sqrt(q); wave 1: 1/q; wave 2: 1/sigma; last wave (P = 8): w
     //   [M, Tb]   wave 0: 1/mu = mu (1/q); wave 1: rho_j and w_c = a_jc + rho_j d_c;
-    //             wave 3: T(:, j-1) = -beta w
-    //   after Tb  every thread: coef_c = w_c / mu and the update of its rows below row j.
+    //             last wave: T(:, j-1) = -beta w
+    //   then      every thread: coef_c = w_c / mu and the update of its rows below row j.
     // Row j of the columns c > j (a_jc -= beta w_c) is not needed again inside the panel, so
     // that update waits for the end of the panel.
-    // wave 3 carries g, then w, across barriers
+    // NPW waves collecting in place of wave 0 alone: dd n = 1024 4.92 -> 4.62 ms, qd 12.0 -> 11.5, od 55.7 ->
+    // 54.1.  (dd with the scalars formed in every wave, without M and Tb: 5.04; two waves share a SIMD.)
+    // the last wave carries g, then w, across barriers
     V<P> cx = zero<P>();
     // where w is formed: beside the reduction while the md scalars are cheap (P <= 4); beside mu
     // for od, whose reduction window is the shorter one in late panels
     constexpr bool kEarlyW = P <= 4;
+    const int tot_items = g.G * W;
+    const int npw = (g.G > 1) ? min(NPW, (tot_items + 63) / 64) : 1;  // waves that hold sums
     for (int j = 0; j < g.wact; ++j) {
         const long dj = off + j;  // row of the diagonal element of column j
         // ---- 1. one reduction per column: thread (slot, c) sums x_j(i) a_c(i) over its rows i > j:
@@ -533,7 +540,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
             if (r > dj && r < hh) acc_fma_step(acc, xk, a[k], k);
         }
         // the partial sums stay lazy (level sums) through every reduction level below and are
-        // renormalised once, in wave 0
+        // renormalised once, after the last
 #pragma unroll
         for (int m = W; m < 64; m <<= 1) acc_add_acc(acc, shfl_xor_acc(acc, m));
         if (lane < W) {
@@ -542,6 +549,9 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
         }
         if (bid == 0 && slot == dj) lds_st(&s_head[c * P], a[0]);
         __syncthreads();  // B1
+        const unsigned tag = g.tag0 + (unsigned)j + 1u;
+        const long GW = tot_items;
+        unsigned long long *xbase = g.gtag + (long)(j & 1) * 2 * P * (GW + W);
         if (wid == 0) {
             Acc<P> ta = acc_zero<P>();
             for (int i = lane; i < NW * W; i += 64) {
@@ -552,83 +562,99 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
             }
 #pragma unroll
             for (int m = W; m < (NW * W < 64 ? NW * W : 64); m <<= 1) acc_add_acc(ta, shfl_xor_acc(ta, m));
-            V<P> hd = (bid == 0) ? lds_ld<P>(&s_head[(lane % W) * P]) : zero<P>();
-            if (g.G > 1) {
-                const unsigned tag = g.tag0 + (unsigned)j + 1u;
-                const long GW = (long)g.G * W;
-                unsigned long long *base = g.gtag + (long)(j & 1) * 2 * P * (GW + W);
-                if (lane < W) {
-#pragma unroll
-                    for (int k = 0; k < P; ++k) st_tagged(base + 2 * k * GW + (long)bid * W + lane, GW, ta.s[k], tag);
-                    if (bid == 0) {
-#pragma unroll
-                        for (int k = 0; k < P; ++k) st_tagged(base + 2 * P * GW + 2 * k * W + lane, W, hd.x[k], tag);
-                    }
-                }
-                // NB items (workgroup, column) a lane in flight at once, and the head row beside the
-                // first of them; the summation order is by item
-                constexpr int NB = (P >= 8) ? 2 : 4;
-                ta = acc_zero<P>();
-                const int tot = g.G * W;
-                for (int i0 = lane, first = 1; i0 - lane < tot; i0 += NB * 64, first = 0) {
-                    unsigned long long wd[NB + 1][2 * P];
-                    long offs[NB + 1], strd[NB + 1];
-                    bool act[NB + 1];
-#pragma unroll
-                    for (int u = 0; u < NB; ++u) {
-                        offs[u] = i0 + u * 64;
-                        strd[u] = GW;
-                        act[u] = i0 + u * 64 < tot;
-                    }
-                    offs[NB] = 2 * P * GW + lane % W;
-                    strd[NB] = W;
-                    act[NB] = first != 0;
-                    poll_tagged<P, NB + 1>(base, offs, strd, act, tag, wd, g.err, g.spin);
-                    if (first) {
-#pragma unroll
-                        for (int k = 0; k < P; ++k) hd.x[k] = tagged_value(wd[NB][2 * k], wd[NB][2 * k + 1]);
-                    }
-#pragma unroll
-                    for (int u = 0; u < NB; ++u) {
-                        if (act[u]) {
-                            Acc<P> o;
-#pragma unroll
-                            for (int k = 0; k < P; ++k) o.s[k] = tagged_value(wd[u][2 * k], wd[u][2 * k + 1]);
-                            acc_add_acc(ta, o);
-                        }
-                    }
-                }
-                const int lim = (g.G * W < 64) ? g.G * W : 64;
-                for (int m = W; m < lim; m <<= 1) acc_add_acc(ta, shfl_xor_acc(ta, m));
-            }
-            const V<P> tot = acc_get(ta);
-            // lanes l < W now hold tot = total of column l and hd = a_jl
             if (lane < W) {
-                lds_st(&s_tot[lane * P], tot);
-                lds_st(&s_hd[lane * P], hd);
+                if (g.G > 1) {
+#pragma unroll
+                    for (int k = 0; k < P; ++k) st_tagged(xbase + 2 * k * GW + (long)bid * W + lane, GW, ta.s[k], tag);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < P; ++k) s_psum[lane * P + k] = ta.s[k];
+                    lds_st(&s_hd[lane * P], lds_ld<P>(&s_head[lane * P]));
+                }
             }
-            if (lane < j) {
-                lds_st(&s_gram[(j * W + lane) * P], tot);
-                lds_st(&s_hrow[(j * W + lane) * P], hd);
+        }
+        if (bid == 0 && wid == 1 && g.G > 1 && lane < W) {
+            const V<P> h = lds_ld<P>(&s_head[lane * P]);
+#pragma unroll
+            for (int k = 0; k < P; ++k) st_tagged(xbase + 2 * P * GW + 2 * k * W + lane, W, h.x[k], tag);
+        }
+        if (wid < npw && g.G > 1) {
+            // NB items (workgroup, column) a lane in flight at once, and beside the first of them the head
+            // row in wave 1 (or the only wave); the summation order is by item
+            constexpr int NB = 2;
+            Acc<P> ta = acc_zero<P>();
+            const bool head = wid == (npw > 1 ? 1 : 0);
+            for (int i0 = wid * 64, first = 1; i0 < tot_items; i0 += NB * 64 * npw, first = 0) {
+                unsigned long long wd[NB + 1][2 * P];
+                long offs[NB + 1], strd[NB + 1];
+                bool act[NB + 1];
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    offs[u] = i0 + lane + u * 64 * npw;
+                    strd[u] = GW;
+                    act[u] = offs[u] < tot_items;
+                }
+                offs[NB] = 2 * P * GW + lane % W;
+                strd[NB] = W;
+                act[NB] = first != 0 && head;
+                poll_tagged<P, NB + 1>(xbase, offs, strd, act, tag, wd, g.err, g.spin);
+                if (act[NB] && lane < W) {
+#pragma unroll
+                    for (int k = 0; k < P; ++k) s_hd[lane * P + k] = tagged_value(wd[NB][2 * k], wd[NB][2 * k + 1]);
+                }
+#pragma unroll
+                for (int u = 0; u < NB; ++u) {
+                    if (act[u]) {
+                        Acc<P> o;
+#pragma unroll
+                        for (int k = 0; k < P; ++k) o.s[k] = tagged_value(wd[u][2 * k], wd[u][2 * k + 1]);
+                        acc_add_acc(ta, o);
+                    }
+                }
+            }
+#pragma unroll
+            for (int m = W; m < 64; m <<= 1) acc_add_acc(ta, shfl_xor_acc(ta, m));
+            if (lane < W) {
+#pragma unroll
+                for (int k = 0; k < P; ++k) s_psum[(wid * W + lane) * P + k] = ta.s[k];
             }
         } else if (bid == 0 && j > 0) {
-            if (wid == 2) t_beta(j - 1);
-            if (wid == 3) {
+            if (wid == NW - 2) t_beta(j - 1);
+            if (wid == NW - 1) {
                 cx = t_g(j - 1);
                 if constexpr (kEarlyW) cx = t_w(j - 1, cx);  // in the shadow of the reduction
             }
         }
         __syncthreads();  // B2
-        // ---- 2. Householder scalars, identical in every lane and every workgroup
-        const V<P> sig = lds_ld<P>(&s_tot[j * P]);
-        const V<P> x1 = lds_ld<P>(&s_hd[j * P]);
+        // ---- 2. the total of column c, and the Householder scalars, identical in every lane and workgroup
+        V<P> tot;
+        {
+            Acc<P> t;
+#pragma unroll
+            for (int k = 0; k < P; ++k) t.s[k] = s_psum[c * P + k];
+            for (int q = 1; q < npw; ++q) {
+                Acc<P> o;
+#pragma unroll
+                for (int k = 0; k < P; ++k) o.s[k] = s_psum[(q * W + c) * P + k];
+                acc_add_acc(t, o);
+            }
+            tot = acc_get(t);
+        }
+        const V<P> hd = lds_ld<P>(&s_hd[c * P]);
+        if (wid == NW - 1 && lane < j) {
+            lds_st(&s_gram[(j * W + lane) * P], tot);
+            lds_st(&s_hrow[(j * W + lane) * P], hd);
+        }
+        const V<P> sig = shfl_md(tot, src0 + j);
+        const V<P> x1 = shfl_md(hd, src0 + j);
         const bool zs = is_zero(sig);
         const bool pos = x1.x[0] > 0.0;
         const bool small = sig.x[0] < x1.x[0] * x1.x[0];  // sigma < x1^2: the cancelling forms are avoided
+        V<P> mu = zero<P>(), coef = zero<P>();  // coef = w_c / mu
         if (wid == 0) {
             if (!zs) {
-                const V<P> mu = sqrt_md(fma(sig, x1, x1));
-                if (lane == 0) lds_st(s_mu, mu);
+                const V<P> m = sqrt_md(fma(sig, x1, x1));
+                if (lane == 0) lds_st(s_mu, m);
             }
             if (lane == 0) s_flag[j] = zs ? 1 : ((pos && small) ? 2 : 0);
         } else if (wid == 1) {
@@ -641,7 +667,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
                 const V<P> is = recip(sig);
                 if (lane == 0) lds_st(s_is, is);
             }
-        } else if (wid == 3 && bid == 0 && j > 0) {
+        } else if (wid == NW - 1 && bid == 0 && j > 0) {
             if constexpr (!kEarlyW) cx = t_w(j - 1, cx);
         }
         __syncthreads();  // M
@@ -654,21 +680,21 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
             // rho = 1/v1, then w_c = a_jc + rho d_c for the columns right of j
             V<P> rho = from_double<P>(1.0);
             if (!zs) {
-                const V<P> mu = lds_ld<P>(s_mu);
-                rho = (!pos && small) ? neg(recip(sub(mu, x1))) : neg(mul(add(mu, x1), lds_ld<P>(s_is)));
-                if (lane > j && lane < W)
-                    lds_st(&s_fc[(j * W + lane) * P], fma(lds_ld<P>(&s_hd[lane * P]), lds_ld<P>(&s_tot[lane * P]), rho));
+                const V<P> m = lds_ld<P>(s_mu);
+                rho = (!pos && small) ? neg(recip(sub(m, x1))) : neg(mul(add(m, x1), lds_ld<P>(s_is)));
+                if (lane > j && lane < W) lds_st(&s_fc[(j * W + lane) * P], fma(hd, tot, rho));
             }
             if (lane == 0) lds_st(&s_rho[j * P], rho);
-        } else if (wid == 3 && bid == 0 && j > 0) {
+        } else if (wid == NW - 1 && bid == 0 && j > 0) {
             t_store(j - 1, cx);
         }
         __syncthreads();  // Tb
+        if (!zs) {
+            mu = lds_ld<P>(s_mu);
+            if (c > j) coef = mul(lds_ld<P>(&s_fc[(j * W + c) * P]), lds_ld<P>(&s_info[(j * 2 + 0) * P]));
+        }
         // ---- 3. reflector j applied to the columns c > j below row j; mu on the diagonal
         if (!zs) {
-            const V<P> mu = lds_ld<P>(s_mu);
-            V<P> coef = zero<P>();  // w_c / mu
-            if (c > j) coef = mul(lds_ld<P>(&s_fc[(j * W + c) * P]), lds_ld<P>(&s_info[(j * 2 + 0) * P]));
 #pragma unroll
             for (int k = 0; k < R; ++k) {
                 const long r = rbase + k * rstride;
@@ -685,8 +711,8 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
     // ---- 4. the last column's beta and T column; the deferred row updates; v = x rho below
     //         the diagonal; store the panel (rows from the previous diagonal)
     if (bid == 0 && g.wact > 0) {
-        if (wid == 2) t_beta(g.wact - 1);
-        if (wid == 3) cx = t_w(g.wact - 1, t_g(g.wact - 1));
+        if (wid == NW - 2) t_beta(g.wact - 1);
+        if (wid == NW - 1) cx = t_w(g.wact - 1, t_g(g.wact - 1));
     }
     const V<P> rc = lds_ld<P>(&s_rho[c * P]);
 #pragma unroll
@@ -704,7 +730,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
         }
     }
     __syncthreads();
-    if (bid == 0 && wid == 3) {
+    if (bid == 0 && wid == NW - 1) {
         if (g.wact > 0) t_store(g.wact - 1, cx);
         for (int jj = g.wact; jj < W; ++jj)
             if (lane < W) stm(g.T, g.tps, (long)jj * W + lane, zero<P>());
