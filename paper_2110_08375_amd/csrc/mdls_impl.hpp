@@ -1991,6 +1991,316 @@ __global__ __launch_bounds__(kThreads) void k_bs_upd(const double *Rc, long ldr,
     }
 }
 
+// ============================================================================ one-launch back substitution
+// R x = y for one right-hand side, every row block of kTrB rows by its own workgroup (Algorithm 1's sweep
+// turned into a data flow): workgroup b owns row block j = nblk - 1 - b, inverts its diagonal block U_j, adds
+// R_ji x_i to its sum as the x_i are published, and publishes x_j = U_j^-1 (y_j - sum).
+// The words of x hold a signalling NaN until they are published: no arithmetic result is one, so the data
+// are their own flag and a wait is one polled load.  A workgroup waits
+// for lower-numbered ones only, and workgroups start in order, so the lowest unfinished one always runs
+// whatever is resident; the polls are bounded all the same.  Wave w holds rows 4 w .. 4 w + 3, its lanes 16
+// columns of each (and the 16 after them): sums over a row stay in the wave.
+// Bound by the chain of nblk steps; the reading of R goes on beside it (the next blocks in flight).  Before,
+// the tiles were inverted in full, b^3/6 multiply-adds each, and every tile took three launches.  n = 128 (tile 32),
+// 1024 (tile 128), 8192 (tile 128), before and now: dd 61, 145, 840 -> 31, 105, 477 us, qd 98, 313, 1693 -> 96, 285,
+// 1298 us; od n = 1024 and 4096 1222, 3724 -> 1259, 3159 us; qd n = 17920, tile 256, 4058 -> 3196 us (past 256 blocks
+// the later workgroups start when the first end, and read R at 1.6 TB/s).
+// AH = 0: the last block's product, its sum, U_j^-1 and another sum all stand between x_{j+1} and x_j.
+// AH = 2: with M_a = U_j^-1 R_{j,j+a}, x_j = z_j - M_2 x_{j+2} - M_1 x_{j+1}, where z_j = U_j^-1 (y_j -
+// sum_{i > j+2} R_ji x_i) is ready before x_{j+2} comes: a step is one exchange, two multiply-adds a thread and
+// one sum in the wave.  The M_a are formed at the start, which costs the first steps their wait (qd 80 us),
+// so this form takes over where the chain is long (trsv_ahead).
+constexpr int kTrB = 32;    // rows of a block
+constexpr int kTrNT = 512;  // threads of a workgroup
+constexpr unsigned long long kTrEmpty = 0x7ff4000000007153ull;
+
+struct TrsvArgs {
+    const double *R;
+    long ldr, psr;
+    const double *y;  // may be x (yps = xps): a workgroup reads only the rows it writes
+    long yps;
+    double *x;
+    long xps;
+    unsigned long long *xw;  // P planes of n words, kTrEmpty on entry
+    int n, nblk;
+    int *err, *d_info;
+    unsigned spin;
+};
+
+template <int P>
+struct TrsvLds {
+    double inv[kTrB * P * kTrB];  // U_j, then its inverse: limb k of column c at (c P + k) kTrB + row
+    double nxt[kTrB * P * kTrB];  // R_{j,j+1}, the same layout
+    double row[2][kTrB * P];      // inversion: the row just formed
+    double diag[kTrB * P];
+    double x[2][2 * kTrB * P];    // x_i, x_{i-1}
+    double v[kTrB * P];           // y_j - sum
+};
+
+template <int P, int AH>
+__global__ __launch_bounds__(kTrNT, 2) void k_trsv(TrsvArgs g)
+{
+    constexpr int B = kTrB, NT = kTrNT;
+    constexpr int U = P <= 4 ? 2 : 1;  // blocks of the sum at a time (od: registers)
+    static_assert(B == 32 && NT == 16 * B, "k_trsv layout");
+    __shared__ TrsvLds<P> lds;
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int j = g.nblk - 1 - (int)blockIdx.x;
+    const int r0 = j * B, nr = min(B, g.n - r0);
+    const int row = 4 * wid + (lane >> 4), c0 = lane & 15;  // columns c0, c0 + 16 of a block
+    const double *Rrow = g.R + r0 + (row < nr ? row : 0);
+    // R_ji and R_j,i-1 at this thread's columns (R_j,i-1 zero where i - 1 is below the sum's last block)
+    V<P> rb[2 * U];
+    auto fetch = [&](int i, int last) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 2 * U; ++t) {
+            const long c = (long)(i - t / 2) * B + c0 + 16 * (t & 1);
+            rb[t] = (c < g.n && i - t / 2 >= last) ? ldm<P>(Rrow, g.psr, c * g.ldr) : zero<P>();
+        }
+    };
+    auto at = [&](const double *m, int c, int r) __attribute__((always_inline)) {
+        V<P> v;
+#pragma unroll
+        for (int k = 0; k < P; ++k) v.x[k] = m[(c * P + k) * B + r];
+        return v;
+    };
+    // the sum over a row's 16 lanes, in every one of them
+    auto row_sum = [&](Acc<P> t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int m = 1; m < 16; m <<= 1) {
+            acc_add_acc(t, shfl_xor_acc(t, m));
+            if (kLazy<P> <= 4 && m == 2) t = acc_from(acc_get(t));
+        }
+        return acc_get(t);
+    };
+    // words of element e of x (zero where e is outside x): loaded, and whether they are there
+    auto load_x = [&](long e, bool want, unsigned long long (&wd)[P]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int w = 0; w < P; ++w)
+            wd[w] = (want && e < g.n)
+                        ? __hip_atomic_load(g.xw + (long)w * g.n + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                        : 0ull;
+    };
+    auto there = [&](const unsigned long long (&wd)[P]) __attribute__((always_inline)) {
+        bool ok = true;
+#pragma unroll
+        for (int w = 0; w < P; ++w) ok = ok && wd[w] != kTrEmpty;
+        return ok;
+    };
+    // after a failed poll: whether to give up
+    auto give_up = [&](unsigned &spins) __attribute__((always_inline)) {
+        if ((spins & 255u) == 255u && __hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return true;
+        if (++spins > g.spin) {
+            __hip_atomic_store(g.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return true;
+        }
+        return false;
+    };
+    auto value = [&](const unsigned long long (&wd)[P]) __attribute__((always_inline)) {
+        V<P> v;
+#pragma unroll
+        for (int k = 0; k < P; ++k) v.x[k] = __longlong_as_double((long long)wd[k]);
+        return v;
+    };
+
+    const int ib = j + 1 + AH;  // the last block of the sum
+    const V<P> yj = row < nr ? ldm<P>(g.y, g.yps, r0 + row) : zero<P>();
+    if (g.nblk - 1 >= ib) fetch(g.nblk - 1, ib);
+    // ---- U_j^-1: all columns advance together, one row at a time from the bottom; thread (c, gq) holds
+    //      rows gq and gq + 16 of column c.  Then M_j.
+    for (int e = tid; e < B * B; e += NT) {
+        const int r = e % B, c = e / B;
+        const V<P> u = (r <= c && c < nr) ? ldm<P>(g.R, g.psr, (long)(r0 + c) * g.ldr + r0 + r)
+                                          : (r == c ? from_double<P>(1.0) : zero<P>());
+#pragma unroll
+        for (int k = 0; k < P; ++k) lds.inv[(c * P + k) * B + r] = u.x[k];
+    }
+    __syncthreads();
+    if (tid < B) lds_st(&lds.diag[tid * P], recip(at(lds.inv, tid, tid)));
+    {
+        const int c = tid & 31, gq = tid >> 5;
+        Acc<P> a[2];
+        V<P> res[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            a[q] = acc_from(gq + 16 * q == c ? from_double<P>(1.0) : zero<P>());
+            res[q] = zero<P>();
+        }
+        __syncthreads();
+        for (int i = B - 1; i >= 0; --i) {
+            if (gq == (i & 15)) {
+                const V<P> xv = mul(acc_get(i >= 16 ? a[1] : a[0]), lds_ld<P>(&lds.diag[i * P]));
+                lds_st(&lds.row[i & 1][c * P], xv);
+                if (i >= 16)
+                    res[1] = xv;
+                else
+                    res[0] = xv;
+            }
+            __syncthreads();
+            const V<P> xv = neg(lds_ld<P>(&lds.row[i & 1][c * P]));
+            const bool renorm = ((B - i) % kLazy<P>) == 0;
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (gq + 16 * q < i) {
+                    acc_fma(a[q], at(lds.inv, i, gq + 16 * q), xv);
+                    if (renorm) a[q] = acc_from(acc_get(a[q]));
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int k = 0; k < P; ++k) lds.inv[(c * P + k) * B + gq + 16 * q] = res[q].x[k];
+        __syncthreads();
+    }
+    V<P> mj[AH > 0 ? AH : 1][2];  // M_a(row, c0), M_a(row, c0 + 16) at a - 1
+    if constexpr (AH > 0) {
+#pragma unroll
+        for (int a = 0; a < AH; ++a) {
+            const long rc = r0 + (long)B * (a + 1);
+            for (int e = tid; e < B * B; e += NT) {
+                const int r = e % B, c = e / B;
+                const V<P> m = (r < nr && rc + c < g.n) ? ldm<P>(g.R, g.psr, (rc + c) * g.ldr + r0 + r) : zero<P>();
+#pragma unroll
+                for (int k = 0; k < P; ++k) lds.nxt[(c * P + k) * B + r] = m.x[k];
+            }
+            __syncthreads();
+            Acc<P> a0 = acc_zero<P>(), a1 = acc_zero<P>();
+#pragma unroll 1
+            for (int k = 4 * wid, nt = 0; k < B; ++k) {  // U_j^-1 is upper triangular
+                const V<P> u = at(lds.inv, k, row);
+                acc_fma(a0, u, at(lds.nxt, c0, k));
+                acc_fma(a1, u, at(lds.nxt, c0 + 16, k));
+                if (++nt % kLazy<P> == 0) {
+                    a0 = acc_from(acc_get(a0));
+                    a1 = acc_from(acc_get(a1));
+                }
+            }
+            mj[a][0] = acc_get(a0);
+            mj[a][1] = acc_get(a1);
+            __syncthreads();
+        }
+    }
+    // Everything below runs twice: first on nothing, with no wait and no store, so that its instructions are
+    // in this CU's cache when the chain comes by (each step of the chain is another CU's, and fetches of
+    // straight-line code that it had never run cost several us a step).
+    // Wave 0 polls for blocks i and i - 1 at once (a lane an element) while all work on the two before them;
+    // workgroups whose turn is far off poll less often, so that the words the chain waits for are not fought over.
+    unsigned long long wd[P];
+    auto ask = [&](int i) __attribute__((always_inline)) {
+        load_x(lane < B ? (long)i * B + lane : (long)(i - 1) * B + lane - B, lane < B || (U == 2 && i - 1 >= ib), wd);
+    };
+    auto receive = [&](int i, int buf) __attribute__((always_inline)) {  // the words asked for
+        unsigned spins = 0;
+        while (!__all(there(wd))) {
+            if (i > j + 8)
+                __builtin_amdgcn_s_sleep(64);
+            else if (i > ib + 1)
+                __builtin_amdgcn_s_sleep(8);
+            if (give_up(spins)) break;
+            ask(i);
+        }
+        lds_st(&lds.x[buf][lane * P], value(wd));
+    };
+#pragma unroll 1
+    for (int live = P <= 4 ? 0 : 1; live < 2; ++live) {  // od's code exceeds the cache
+        // ---- the sum of R_ji x_i, i >= ib, U blocks at a time
+        Acc<P> acc[2] = {acc_zero<P>(), acc_zero<P>()};
+        const int i1 = live ? g.nblk - 1 : ib - 1;
+        if (wid == 0 && i1 >= ib) {
+            ask(i1);
+            receive(i1, 0);
+        }
+        int nt = 0;
+#pragma unroll 1
+        for (int i = i1, buf = 0; i >= ib; i -= U, buf ^= 1) {
+            V<P> cur[2 * U];
+#pragma unroll
+            for (int t = 0; t < 2 * U; ++t) cur[t] = rb[t];
+            if (i - U >= ib) fetch(i - U, ib);
+            __syncthreads();
+            if (wid == 0 && i - U >= ib) ask(i - U);
+#pragma unroll
+            for (int t = 0; t < 2 * U; ++t)
+                acc_fma(acc[t & 1], cur[t], lds_ld<P>(&lds.x[buf][(c0 + 16 * t) * P]));
+            nt += U;
+            if (nt % kLazy<P> == 0) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) acc[t] = acc_from(acc_get(acc[t]));
+            }
+            if (wid == 0 && i - U >= ib) receive(i - U, buf ^ 1);
+        }
+        acc_add_acc(acc[0], acc[1]);
+        const V<P> sum = row_sum(acc_from(acc_get(acc[0])));
+        if (c0 == 0) lds_st(&lds.v[row * P], row < nr ? sub(yj, sum) : zero<P>());
+        __syncthreads();
+        // ---- z_j = U_j^-1 (y_j - sum), x_j = z_j - M_2 x_{j+2} - M_1 x_{j+1}
+        V<P> xj;
+        {
+            Acc<P> t0 = acc_zero<P>(), t1 = acc_zero<P>();
+            acc_fma(t0, at(lds.inv, c0, row), lds_ld<P>(&lds.v[c0 * P]));
+            acc_fma(t1, at(lds.inv, c0 + 16, row), lds_ld<P>(&lds.v[(c0 + 16) * P]));
+            acc_add_acc(t0, t1);
+            xj = row_sum(t0);
+        }
+        if constexpr (AH > 0) {
+#pragma unroll
+            for (int a = AH - 1; a >= 0; --a) {
+                if (j + 1 + a >= g.nblk) continue;
+                V<P> xv[2];
+                unsigned long long wa[P], wb[P];
+                unsigned spins = 0;
+                for (;;) {  // every wave polls for itself: this lane's two elements
+                    load_x((long)(j + 1 + a) * B + c0, true, wa);
+                    load_x((long)(j + 1 + a) * B + c0 + 16, true, wb);
+                    if (__all(there(wa) && there(wb)) || !live || give_up(spins)) break;
+                }
+                xv[0] = value(wa);
+                xv[1] = value(wb);
+                Acc<P> t0 = acc_zero<P>(), t1 = acc_zero<P>();
+                acc_fma(t0, mj[a][0], xv[0]);
+                acc_fma(t1, mj[a][1], xv[1]);
+                acc_add_acc(t0, t1);
+                xj = sub(xj, row_sum(t0));
+            }
+        }
+        if (live && c0 == 0 && row < nr) {
+#pragma unroll
+            for (int k = 0; k < P; ++k)
+                __hip_atomic_store(g.xw + (long)k * g.n + r0 + row, (unsigned long long)__double_as_longlong(xj.x[k]),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            stm(g.x, g.xps, r0 + row, xj);
+        }
+        __syncthreads();  // lds.v is written again
+    }
+    // the workgroup of the first rows is the last to finish: it has waited for all the others
+    if (j == 0 && tid == 0 && __hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) *g.d_info = -1;
+}
+
+namespace {
+// before k_trsv: every word of x empty, *d_info = smallest 1-based i with R(i,i) exactly zero, else 0, and with
+// clear_err the time-out flag
+__global__ __launch_bounds__(kThreads) void k_trsv_init(unsigned long long *xw, long nw, int *err, int clear_err,
+                                                       const double *R, long ldr, long ps, int n, int P, int *d_info)
+{
+    for (long i = (long)blockIdx.x * kThreads + threadIdx.x; i < nw; i += (long)gridDim.x * kThreads) xw[i] = kTrEmpty;
+    if (blockIdx.x != 0) return;
+    __shared__ int smin;
+    if (threadIdx.x == 0) {
+        smin = INT_MAX;
+        if (clear_err) *err = 0;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += kThreads) {
+        bool z = true;
+        for (int k = 0; k < P; ++k) z = z && (R[k * ps + (long)i * ldr + i] == 0.0);
+        if (z) atomicMin(&smin, i);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) *d_info = (smin == INT_MAX) ? 0 : smin + 1;
+}
+}  // namespace
+
 // ============================================================================ T, W, Q^T B helpers
 // W(r, k*tile + j) = -sum_{l<=j} Y_k(r, l) T_k(l, j) for r >= k*tile; zero above.
 template <int P>
@@ -2846,13 +3156,33 @@ void backsub_sweep(const Ctx<P> &cx, int n, int tile, const double *R, long ldr,
     }
 }
 
-// tiled back substitution of y (P planes of n, in ws.yw); x receives the solution
+// More row blocks than this and k_trsv works ahead of the chain (AH = 2).  n = 1024 (32 blocks) with AH = 2
+// and with AH = 0: dd 105 and 121 us, qd 285 and 322, od 1259 and 1400; n = 300 (10 blocks): dd 70 and 50,
+// qd 187 and 142, od 821 and 562.
 template <int P>
-void backsub_tiles(const Ctx<P> &cx, int n, int tile, const double *R, long ldr, long psr, double *x, long xps,
-                   int *d_info)
+constexpr int trsv_ahead()
 {
-    backsub_prep<P>(cx, n, tile, R, ldr, psr, cx.big(), d_info);
-    backsub_sweep<P>(cx, n, tile, R, ldr, psr, cx.big(), cx.yw(), x, xps, nullptr);
+    return 22;
+}
+
+// Back substitution R x = y (y: P planes yps apart, may be x) in two launches; the words of x lie in the
+// trailing update's partial sums.  *d_info: the first exactly zero R(k,k), -1 for a time-out.
+template <int P>
+void backsub_solve(const Ctx<P> &cx, int n, const double *R, long ldr, long psr, const double *y, long yps, double *x,
+                   long xps, int *d_info, bool clear_err)
+{
+    unsigned long long *xw = (unsigned long long *)cx.apart();
+    const long nw = (long)P * n;
+    const int nblk = (n + kTrB - 1) / kTrB;
+    const int grid = (int)std::min<long>(256, (nw + kThreads - 1) / kThreads);
+    MDLS_LAUNCH("k_trsv_init", P, 0, k_trsv_init, dim3(grid), dim3(kThreads), cx.s, xw, nw, cx.err(), clear_err ? 1 : 0, R,
+                ldr, psr, n, P, d_info);
+    const TrsvArgs ta{R, ldr, psr, y, yps, x, xps, xw, n, nblk, cx.err(), d_info, tuning().spin_limit};
+    const double work = 0.5 * n * n + (double)nblk * kTrB * kTrB * kTrB / 6.0;
+    if (nblk > trsv_ahead<P>())
+        MDLS_LAUNCH("k_trsv", P, work, (k_trsv<P, 2>), dim3(nblk), dim3(kTrNT), cx.s, ta);
+    else
+        MDLS_LAUNCH("k_trsv", P, work, (k_trsv<P, 0>), dim3(nblk), dim3(kTrNT), cx.s, ta);
 }
 
 template <int P>
@@ -2861,9 +3191,7 @@ int solve_t(int m, int n, int tile, double *A, int lda, double *b, double *x, vo
     Ctx<P> cx{(char *)ws, layout(P, m, n, tile), s};
     const long psa = (long)lda * n;
     if (qr_panels<P>(cx, m, n, A, lda, psa, b, m, m, 1) != 0) return MDLS_EHIP;
-    MDLS_LAUNCH("k_copy", P, 0, k_copy, dim3((n + 255) / 256), dim3(256), s, b, (long)m, cx.yw(), (long)n, n, P);
-    backsub_tiles<P>(cx, n, tile, A, lda, psa, x, n, d_info);
-    MDLS_LAUNCH("k_fold_err", P, 0, k_fold_err, dim3(1), dim3(64), s, cx.err(), d_info);
+    backsub_solve<P>(cx, n, A, lda, psa, b, m, x, n, d_info, false);
     return hipGetLastError() == hipSuccess ? 0 : MDLS_EHIP;
 }
 
@@ -3028,8 +3356,7 @@ template <int P>
 int backsub_t(int n, int tile, const double *R, int ldr, double *x, void *ws, int *d_info, hipStream_t s)
 {
     Ctx<P> cx{(char *)ws, layout(P, n, n, tile), s};
-    MDLS_LAUNCH("k_copy", P, 0, k_copy, dim3((n + 255) / 256), dim3(256), s, x, (long)n, cx.yw(), (long)n, n, P);
-    backsub_tiles<P>(cx, n, tile, R, ldr, (long)ldr * n, x, n, d_info);
+    backsub_solve<P>(cx, n, R, ldr, (long)ldr * n, x, n, x, n, d_info, true);
     return hipGetLastError() == hipSuccess ? 0 : MDLS_EHIP;
 }
 

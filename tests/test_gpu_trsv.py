@@ -1,0 +1,81 @@
+"""GPU parity of the one-launch back substitution at the edges of its layout: fewer rows than a block
+of 32, one more and one less than a block, an odd number of blocks, around the number of blocks from
+which it works ahead of the chain (22), a leading dimension larger than n."""
+import numpy as np
+import pytest
+
+import mdgen
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def unit(P):
+    return 2.0 ** -(53 * P - (P - 1))
+
+
+def md_err(x, ref):
+    d = np.zeros(ref.shape[1:])
+    for k in range(ref.shape[0] - 1, -1, -1):
+        d = d + (x[k] - ref[k])
+    return np.max(np.abs(d)) / np.max(np.abs(ref[0]))
+
+
+def problem(P, n, ldr):
+    R = np.full((P, n, ldr), np.nan)  # what lies below the diagonal is not read
+    U = mdgen.upper_triangular(P, n, 40 + n, well_conditioned=True)
+    for c in range(n):
+        R[:, c, :c + 1] = U[:, c, :c + 1]
+    return U, R, mdgen.md_vector(P, n, 41, mdgen.STREAM_B)
+
+
+SIZES = [(1, 1), (5, 5), (31, 31), (32, 40), (33, 33), (64, 64), (65, 65), (96, 97), (703, 703), (704, 704), (705, 710),
+         (737, 737)]
+
+
+@pytest.mark.parametrize("P", (1, 2, 4))
+@pytest.mark.parametrize("n,ldr", SIZES)
+def test_trsv_edges(orc, P, n, ldr):
+    check(orc, P, n, ldr)
+
+
+@pytest.mark.parametrize("n,ldr", [(1, 1), (33, 33), (64, 70), (90, 90), (736, 736)])
+def test_trsv_edges_od(orc, n, ldr):
+    check(orc, 8, n, ldr)
+
+
+def check(orc, P, n, ldr):
+    import paper_2110_08375_amd as M
+
+    print("case trsv P=%d n=%d ldr=%d" % (P, n, ldr), flush=True)
+    U, R, y = problem(P, n, ldr)
+    x, info = M.backsub(P, torch.from_numpy(R).cuda(), torch.from_numpy(y).cuda(), 1)
+    assert int(info.item()) == 0
+    ref, _ = orc.backsub(U, y)
+    k = float(np.linalg.cond(U[0].T))
+    err = md_err(x.cpu().numpy(), ref)
+    print("  %.2f u kappa" % (err / (unit(P) * k)), flush=True)
+    assert err <= 64 * n * unit(P) * max(1.0, k)
+
+
+def test_trsv_status():
+    """A zero diagonal entry is reported (the first one), and a wait that gives up at once ends with -1."""
+    import paper_2110_08375_amd as M
+    from paper_2110_08375_amd import mdls
+
+    U, _, y = problem(2, 150, 150)
+    U[:, 120, 120] = 0.0
+    U[:, 77, 77] = 0.0
+    _, info = M.backsub(2, torch.from_numpy(U).cuda(), torch.from_numpy(y).cuda(), 1)
+    assert int(info.item()) == 78
+    U, _, y = problem(2, 1500, 1500)
+    Ug = torch.from_numpy(U).cuda()
+    saved = M.get_tuning(mdls.MDLS_TUNE_SPIN_LIMIT)
+    M.set_tuning(mdls.MDLS_TUNE_SPIN_LIMIT, 0)
+    try:
+        _, info = M.backsub(2, Ug, torch.from_numpy(y).cuda(), 1)
+        assert int(info.item()) == -1
+    finally:
+        M.set_tuning(mdls.MDLS_TUNE_SPIN_LIMIT, saved)
+    _, info = M.backsub(2, Ug, torch.from_numpy(y).cuda(), 1)
+    assert int(info.item()) == 0
