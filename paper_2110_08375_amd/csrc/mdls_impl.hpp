@@ -350,24 +350,38 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
         }
         return gv;
     };
-    // lane l < jj: w_l = sum_{l <= k < jj} T(l, k) g(k, jj); even and odd k in two
-    // accumulators, so the two halves of the sum overlap
+    // lane l < jj: w_l = sum_{l <= k < jj} T(l, k) g(k, jj).  W <= 8: a lane forms one product (l = lane / W,
+    // k = lane % W) and the W lanes of an l are summed (od n = 1024: SOMETHING); W = 16: lane l
+    // sums, even and odd k in two accumulators, so the two halves of the sum overlap
     auto t_w = [&](int jj, const V<P> &gv) __attribute__((always_inline)) {
-        Acc<P> w0 = acc_zero<P>(), w1 = acc_zero<P>();
+        Acc<P> w0 = acc_zero<P>();
+        if constexpr (W * W <= 64) {
+            const int l = lane / W, k = lane % W;
+            const V<P> gk = shfl_md(gv, k);
+            if (l < W && l <= k && k < jj) {
+                const V<P> t = lds_ld<P>(&s_T[(k * W + l) * P]);
+                casc_fma<P, P, P, 0, 0, false>(w0.s, t.x, gk.x, nullptr);
+            }
 #pragma unroll
-        for (int k = 0; k < W; ++k) {
-            if (k < jj) {
-                const V<P> gk = shfl_md(gv, k);
-                if (lane <= k) {
-                    if (k & 1)
-                        acc_fma(w1, lds_ld<P>(&s_T[(k * W + lane) * P]), gk);
-                    else
-                        acc_fma(w0, lds_ld<P>(&s_T[(k * W + lane) * P]), gk);
+            for (int m = 1; m < W; m <<= 1) acc_add_acc(w0, shfl_xor_acc(w0, m));
+            return shfl_md(acc_get(w0), (lane % W) * W);
+        } else {
+            Acc<P> w1 = acc_zero<P>();
+#pragma unroll
+            for (int k = 0; k < W; ++k) {
+                if (k < jj) {
+                    const V<P> gk = shfl_md(gv, k);
+                    if (lane <= k) {
+                        if (k & 1)
+                            acc_fma(w1, lds_ld<P>(&s_T[(k * W + lane) * P]), gk);
+                        else
+                            acc_fma(w0, lds_ld<P>(&s_T[(k * W + lane) * P]), gk);
+                    }
                 }
             }
+            acc_add_acc(w0, w1);
+            return acc_get(w0);
         }
-        acc_add_acc(w0, w1);
-        return acc_get(w0);
     };
     // T(0:jj, jj) = -beta_jj w, T(jj, jj) = beta_jj, zero below
     auto t_store = [&](int jj, const V<P> &w) __attribute__((always_inline)) {
