@@ -29,10 +29,12 @@
 #include <cstdlib>
 #include <functional>
 #include <queue>
+#include <type_traits>
 #include <vector>
 
 #pragma once
 #include "mdls.h"
+#include "md_lanes.hpp"
 #include "mdls_kernels.hpp"
 #include "mdls_split_kernels.hpp"
 
@@ -297,6 +299,7 @@ struct PanelLds {
     double rho[W * P];
     double beta[W * P];
     double T[W * W * P];     // T, column-major
+    double dig[2][64];       // digits of mu and 1/sigma (md_lanes.hpp)
     int flag[W];             // per column: 1 sigma == 0, 2 beta from rho (x1 > 0, sigma < x1^2)
 };
 
@@ -665,21 +668,47 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
         const bool pos = x1.x[0] > 0.0;
         const bool small = sig.x[0] < x1.x[0] * x1.x[0];  // sigma < x1^2: the cancelling forms are avoided
         V<P> mu = zero<P>(), coef = zero<P>();  // coef = w_c / mu
+        // od spreads mu, 1/mu, 1/sigma and rho over the lanes (md_lanes.hpp) while the exponents leave room;
+        // NaN, infinities and the rest take the one-lane forms
+        const double q0 = __builtin_fma(x1.x[0], x1.x[0], sig.x[0]);
+        const bool spread = P >= 8 && q0 < 0x1p900 && sig.x[0] > 0x1p-900;
+        const int pe = spread ? ilogb(q0) >> 1 : 0, se = spread ? ilogb(sig.x[0]) : 0;
         if (wid == 0) {
-            if (!zs) {
+            if (!zs && spread) {
+                if constexpr (P >= 8) {
+                    constexpr int L = lanes::kDigits<P>;
+                    const double X1 = lanes::digits<P, P>(x1.x, pe, lane);
+                    const double Q = lanes::carry(
+                        lanes::mul<L>(X1, X1, lane) + lanes::digits<P, P>(sig.x, 2 * pe, lane), lane);
+                    const double Y = lanes::rsqrt<P>(Q, __builtin_ldexp(q0, -2 * pe), lane);
+                    const double S = lanes::mul<L>(Q, Y, lane);
+                    lds.dig[0][lane] = S;
+                    const V<P> m = lanes::limbs<P>(S, pe), im = lanes::limbs<P>(Y, -pe);
+                    if (lane == 0) {
+                        lds_st(s_mu, m);
+                        lds_st(s_iq, im);  // 1/mu here
+                    }
+                }
+            } else if (!zs) {
                 const V<P> m = sqrt_md(fma(sig, x1, x1));
                 if (lane == 0) lds_st(s_mu, m);
             }
             if (lane == 0) s_flag[j] = zs ? 1 : ((pos && small) ? 2 : 0);
         } else if (wid == 1) {
-            if (!zs) {
+            if (!zs && !spread) {
                 const V<P> iq = recip(fma(sig, x1, x1));
                 if (lane == 0) lds_st(s_iq, iq);
             }
         } else if (wid == 2) {
             if (!zs && (pos || !small)) {
-                const V<P> is = recip(sig);
-                if (lane == 0) lds_st(s_is, is);
+                if (spread) {
+                    if constexpr (P >= 8)
+                        lds.dig[1][lane] = lanes::recip<P>(lanes::digits<P, P>(sig.x, se, lane),
+                                                           __builtin_ldexp(sig.x[0], -se), lane);
+                } else {
+                    const V<P> is = recip(sig);
+                    if (lane == 0) lds_st(s_is, is);
+                }
             }
         } else if (wid == NW - 1 && bid == 0 && j > 0) {
             if constexpr (!kEarlyW) cx = t_w(j - 1, cx);
@@ -687,15 +716,30 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
         __syncthreads();  // M
         if (wid == 0) {
             if (!zs && lane == 0) {
-                lds_st(&s_info[(j * 2 + 0) * P], mul(lds_ld<P>(s_mu), lds_ld<P>(s_iq)));  // 1/mu
+                const V<P> iq = lds_ld<P>(s_iq);
+                lds_st(&s_info[(j * 2 + 0) * P], spread ? iq : mul(lds_ld<P>(s_mu), iq));  // 1/mu
                 lds_st(&s_info[(j * 2 + 1) * P], x1);
             }
         } else if (wid == 1) {
             // rho = 1/v1, then w_c = a_jc + rho d_c for the columns right of j
             V<P> rho = from_double<P>(1.0);
             if (!zs) {
-                const V<P> m = lds_ld<P>(s_mu);
-                rho = (!pos && small) ? neg(recip(sub(m, x1))) : neg(mul(add(m, x1), lds_ld<P>(s_is)));
+                if (spread) {
+                    if constexpr (P >= 8) {
+                        const double S = lds.dig[0][lane], X1 = lanes::digits<P, P>(x1.x, pe, lane);
+                        if (!pos && small) {
+                            const double D = lanes::carry(S - X1, lane);  // mu - x1, in [1, 4)
+                            const double d0 = __builtin_ldexp(s_mu[0] - x1.x[0], -pe);
+                            rho = lanes::limbs<P>(-lanes::recip<P>(D, d0, lane), -pe);
+                        } else {
+                            const double F = lanes::carry(S + X1, lane);
+                            rho = lanes::limbs<P>(-lanes::mul<lanes::kDigits<P>>(F, lds.dig[1][lane], lane), pe - se);
+                        }
+                    }
+                } else {
+                    const V<P> m = lds_ld<P>(s_mu);
+                    rho = (!pos && small) ? neg(recip(sub(m, x1))) : neg(mul(add(m, x1), lds_ld<P>(s_is)));
+                }
                 if (lane > j && lane < W) lds_st(&s_fc[(j * W + lane) * P], fma(hd, tot, rho));
             }
             if (lane == 0) lds_st(&s_rho[j * P], rho);
