@@ -5,8 +5,8 @@
 // digits, lane k holding d_k with value sum_k d_k 2^(-24 k) (times a power of two the caller keeps), each
 // d_k an integer of at most 24 bits and sign in a double, so that a product's columns c_k = sum_i a_i
 // b_(k-i) are exact in double (at most 20 products below 2^47): one broadcast, one FMA and one shift by a
-// lane per digit of a.  Fixed point: the digits reach 2^-456 (P = 8) or 2^-240 (P = 4), well below the last
-// limb of a value in [1/4, 4).  A product of P = 8 takes about 130 instructions in place of 970, the square
+// lane per digit of a.  Fixed point: the digits reach 2^-456, below the last limb of an od value in [1/4, 4).
+// (qd keeps the limbs: its scalars are short enough that the spread form was 5% slower.)  A product takes about 130 instructions in place of 970, the square
 // root with its reciprocal 1.1 K in place of 6 K, and the code is short enough to stay in the instruction
 // cache.
 #pragma once
@@ -16,9 +16,8 @@
 namespace mdk {
 namespace lanes {
 
-template <int P>
-constexpr int kDigits = P >= 8 ? 20 : 11;  // digit 0 is the integer part
-constexpr double kBase = 16777216.0;       // 2^24
+constexpr int kDigits = 20;  // digit 0 is the integer part
+constexpr double kBase = 16777216.0;  // 2^24
 
 // lane k takes lane k - 1's value (lane 0 zero), and lane k + 1's (the last lane zero): DPP shifts
 // of the whole wave by one
@@ -72,15 +71,15 @@ __device__ __forceinline__ double mul(double a, double b, int lane)
 }
 
 // digits of x 2^-e, |x 2^-e| < 2^22: every limb rounded to each digit's grid, less what the digits above took
-template <int P, int NL>
+template <int NL>
 __device__ __forceinline__ double digits(const double *x, int e, int lane)
 {
     double d = 0.0;
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-        const double a = lane < kDigits<P> ? __builtin_rint(__builtin_ldexp(x[i], 24 * lane - e)) : 0.0;
+        const double a = lane < kDigits ? __builtin_rint(__builtin_ldexp(x[i], 24 * lane - e)) : 0.0;
         const double up = shift_up(a);
-        d += lane < kDigits<P> ? __builtin_fma(-kBase, up, a) : 0.0;
+        d += lane < kDigits ? __builtin_fma(-kBase, up, a) : 0.0;
     }
     return d;
 }
@@ -90,7 +89,7 @@ __device__ __forceinline__ double digits(const double *x, int e, int lane)
 template <int P>
 __device__ __forceinline__ V<P> limbs(double d, int e)
 {
-    constexpr int N = kDigits<P> / 2 + kDigits<P> % 2;
+    constexpr int N = kDigits / 2;
     const double v = __builtin_fma(shift_down(d), 1.0 / kBase, d);
     double x[N];
 #pragma unroll
@@ -116,13 +115,10 @@ __device__ __forceinline__ V<P> limbs(double d, int e)
 // 1/sqrt(Q) for Q in [1, 4), q its leading double.  y (1 + e/2 + 3 e^2/8) with e = 1 - Q y^2 triples the bits:
 // 52 -> 154 -> 460.  e/2 + 3 e^2/8 is kept as eighths, and the product's eighths are brought back to whole digits
 // one lane further down (2^-3 = 2^21 2^-24).
-template <int P>
 __device__ __forceinline__ double rsqrt(double Q, double q, int lane)
 {
-    constexpr int L = kDigits<P>;
-    constexpr int N2 = L < 8 ? L : 8, M2 = L < 16 ? L : 16, E2 = L < 14 ? L : 14;
     const double y0 = 1.0 / sqrt(q);
-    double y = digits<P, 1>(&y0, 0, lane);
+    double y = digits<1>(&y0, 0, lane);
     auto refine = [&](auto n, auto m, auto k) __attribute__((always_inline)) {
         const double t = mul<decltype(m)::value>(mul<decltype(n)::value>(y, y, lane), Q, lane);
         const double e = (lane == 0 ? 1.0 : 0.0) - t;
@@ -131,27 +127,24 @@ __device__ __forceinline__ double rsqrt(double Q, double q, int lane)
         y = carry(y + carry(shift_up(v * 2097152.0), lane), lane);
     };
     refine(std::integral_constant<int, 4>{}, std::integral_constant<int, 8>{}, std::integral_constant<int, 8>{});
-    y = lane < N2 ? y : 0.0;
-    refine(std::integral_constant<int, N2>{}, std::integral_constant<int, M2>{}, std::integral_constant<int, E2>{});
+    y = lane < 8 ? y : 0.0;
+    refine(std::integral_constant<int, 8>{}, std::integral_constant<int, 16>{}, std::integral_constant<int, 14>{});
     return y;
 }
 
 // 1/X for X in [1, 4), x its leading double: z (1 + r + r^2) with r = 1 - X z
-template <int P>
 __device__ __forceinline__ double recip(double X, double x, int lane)
 {
-    constexpr int L = kDigits<P>;
-    constexpr int N2 = L < 8 ? L : 8, E2 = L < 14 ? L : 14;
     const double z0 = 1.0 / x;
-    double z = digits<P, 1>(&z0, 0, lane);
+    double z = digits<1>(&z0, 0, lane);
     auto refine = [&](auto n, auto k) __attribute__((always_inline)) {
         const double r = (lane == 0 ? 1.0 : 0.0) - mul<decltype(n)::value>(z, X, lane);
         const double u = carry(r + mul<decltype(k)::value>(r, r, lane), lane);
         z = carry(z + mul<decltype(n)::value>(z, u, lane), lane);
     };
     refine(std::integral_constant<int, 4>{}, std::integral_constant<int, 8>{});
-    z = lane < N2 ? z : 0.0;
-    refine(std::integral_constant<int, N2>{}, std::integral_constant<int, E2>{});
+    z = lane < 8 ? z : 0.0;
+    refine(std::integral_constant<int, 8>{}, std::integral_constant<int, 14>{});
     return z;
 }
 

@@ -16,7 +16,7 @@
 //
 // Kernels (one QR panel of b = tile columns at a time):
 //   k_cpanel  -- the whole panel in one persistent launch, one workgroup per column, each
-//                column handed to the later ones through device memory behind a counter;
+//                column handed to the later ones through device memory, word by word;
 //   k_crefl   -- (the panel a launch per column instead) the reflector of its first column;
 //   k_cstep   -- for panel column j: H_j applied to the panel columns right of j, one
 //                workgroup per column; workgroup 0 then forms the reflector of column j+1
@@ -419,12 +419,19 @@ __global__ __launch_bounds__(kThreads) void k_cstep_r(CPanelArgs g)
 // a workspace buffer) and three scalars, not v = x/v1: with iv = 1/v1 and D = sum_{i>j}
 // conj(x_i) a_i, H_j a has w = v^H a = a_j + conj(iv) D, row j becomes a_j - beta w =
 // (1 - beta) a_j + conj(p1) D and the rows below a_i + x_i (p1 a_j + p2 D), where p1 =
-// -beta iv and p2 = -beta |iv|^2.  The owner stages x before its reflector's chain (the stores
-// overlap it), then stores p1, p2, beta, fences (release) and sets *count = c + 1; scaling its
-// rows to v waits until the end, and so does the update of row j by H_j (D is kept in the
-// unused head of the column's own staging slot), so neither is on the chain.  A workgroup
-// waits only for lower-numbered ones and each wait is a bounded poll (a time-out raises *err,
-// after which no wait polls), so the grid always drains.
+// -beta iv and p2 = -beta |iv|^2.  Scaling the rows to v waits until the end, and so does the
+// update of row j by H_j (D is kept in the unused head of the column's own staging slot), so
+// neither is on the chain.
+//
+// The words themselves are the signal: k_cpanel_init fills them with a signalling NaN that no
+// arithmetic makes, a reader polls what it needs until none is left, and x is taken before the
+// scalars.  So there is no counter, no fence and no acquire between two columns, and a reader
+// forms D while the owner still reduces sigma and forms the reflector.  What bounds a column is
+// that chain of two reductions, the reflector and two hand-offs: dd 512, tile 128, 3.9 us (csolve 4.27 ms a
+// launch per column, 3.36 here).  The same with the counter and fences before: csolve dd 512 (tile 32)
+// 4.88 -> 3.69 ms, qd 512 19.4 -> 15.2, od 192 34.3 -> 27.1 ms.  A workgroup waits
+// only for lower-numbered ones and each wait is a bounded poll (a time-out raises *err, after
+// which no wait polls for long), so the grid always drains.
 //
 // The reflector (the same vector as c_reflector's) is formed with a short chain: the four long
 // md operations sqrt(q), 1/q, 1/sqrt(|x1|^2) and 1/sigma (q = |x1|^2 + sigma) run side by side,
@@ -442,7 +449,7 @@ struct CPersistArgs {
     double *xs;    // staged columns: 2P planes of stride xps, panel column b at b * m
     long xps;
     double *rec;   // per column c: p1 (2P doubles), p2, beta (P each) at rec + 4P c
-    unsigned *count;  // columns published in this factorisation; zero before its first panel
+                   // every word of xs and of this panel's rec kTrEmpty on entry
     int *err;         // set to 1 if a wait times out
     unsigned spin;    // polls before a wait gives up
 };
@@ -519,24 +526,28 @@ __device__ __forceinline__ void cst_coherent(double *X, long ps, long off, const
     }
 }
 
-// Wait until *count >= target: thread 0 polls (each poll after a short sleep), giving up after
-// spin polls or once *err is set, then acquires; the barrier passes that on to the other
-// threads, whose reads of published data are coherent loads.  Called by all threads.
-__device__ inline void wait_count(unsigned *count, unsigned target, int *err, unsigned spin)
+// Whether v still is the word that k_cpanel_init left
+__device__ __forceinline__ bool word_empty(double v) { return (unsigned long long)__double_as_longlong(v) == kTrEmpty; }
+
+template <int P>
+__device__ __forceinline__ bool cword_empty(const CV<P> &v)
 {
-    if (threadIdx.x == 0) {
-        unsigned spins = 0;
-        while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            if ((spins & 255u) == 255u && __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
-            __builtin_amdgcn_s_sleep(1);
-            if (++spins > spin) {
-                __hip_atomic_store(err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    bool e = false;
+#pragma unroll
+    for (int k = 0; k < P; ++k) e = e || word_empty(v.re.x[k]) || word_empty(v.im.x[k]);
+    return e;
+}
+
+// v as it may be published: arithmetic never makes that signalling NaN, a copied input may hold it
+template <int P>
+__device__ __forceinline__ CV<P> cword_full(CV<P> v)
+{
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        if (word_empty(v.re.x[k])) v.re.x[k] = __builtin_nan("");
+        if (word_empty(v.im.x[k])) v.im.x[k] = __builtin_nan("");
     }
-    __syncthreads();
+    return v;
 }
 
 template <int P>
@@ -576,30 +587,36 @@ __global__ __launch_bounds__(kThreads) void k_cpanel(CPersistArgs g)
         if (i < h) sst(i, cldm<P>(g.A, g.ps, offc + i));
     }
 
+    // after a failed poll: whether to give up
+    auto give_up = [&](unsigned &spins) __attribute__((always_inline)) {
+        if ((spins & 255u) == 255u && __hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return true;
+        if (++spins > g.spin) {
+            __hip_atomic_store(g.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return true;
+        }
+        __builtin_amdgcn_s_sleep(1);
+        return false;
+    };
+
     // ---- H_j for the columns before c; row jj keeps its value, D goes to the staging slot
     for (int j = g.kt; j < c; ++j) {
         const int jj = j - g.kt;
-        wait_count(g.count, (unsigned)(j + 1), g.err, g.spin);
         const double *rj = g.rec + (long)4 * P * j;
         const double *xj = g.xs + (long)jj * g.m;
-        // the staged column and the scalars together (one round trip)
+        // the staged column: its owner forms the reflector during the dot
         CV<P> x[QM];
+        unsigned spins = 0;
+        for (;;) {
+            bool wait = false;
 #pragma unroll
-        for (int q = 0; q < QM; ++q) {
-            const int i = tid + q * kThreads;
-            x[q] = (i > jj && i < h) ? cld_coherent<P>(xj, g.xps, i) : czero<P>();
+            for (int q = 0; q < QM; ++q) {
+                const int i = tid + q * kThreads;
+                const bool in = i > jj && i < h;
+                x[q] = in ? cld_coherent<P>(xj, g.xps, i) : czero<P>();
+                wait = wait || (in && cword_empty(x[q]));
+            }
+            if (__ballot(wait) == 0 || give_up(spins)) break;
         }
-        CV<P> p1;
-        V<P> p2, bt;
-#pragma unroll
-        for (int e = 0; e < P; ++e) {
-            p1.re.x[e] = ld_coherent(rj + e);
-            p1.im.x[e] = ld_coherent(rj + P + e);
-            p2.x[e] = ld_coherent(rj + 2 * P + e);
-            bt.x[e] = ld_coherent(rj + 3 * P + e);
-        }
-        if (is_zero(bt)) continue;  // identity reflector (uniform)
-        const CV<P> st1 = cmul(p1, sld(jj));  // p1 a_j, beside the dot
         // D: at most 2 QM = 32/P products per part, within kLazy<P>, renormalised at the end
         CAcc<P> acc = cacc_zero<P>();
 #pragma unroll
@@ -607,8 +624,25 @@ __global__ __launch_bounds__(kThreads) void k_cpanel(CPersistArgs g)
             const int i = tid + q * kThreads;
             if (i > jj && i < h) cacc_fma<P, true>(acc, x[q], sld(i));
         }
-        const CV<P> D = cacc_block_total(cacc_from(cacc_get(acc)), sred);
-        CAcc<P> t = cacc_from(st1);
+        const CV<P> D = cacc_block_total(cacc_from(cacc_get(acc)), sred);  // its barriers publish row jj
+        // the scalars, a word a lane
+        double rw = 0.0;
+        spins = 0;
+        for (;;) {
+            if (lane < 4 * P) rw = ld_coherent(rj + lane);
+            if (__ballot(lane < 4 * P && word_empty(rw)) == 0 || give_up(spins)) break;
+        }
+        CV<P> p1;
+        V<P> p2, bt;
+#pragma unroll
+        for (int e = 0; e < P; ++e) {
+            p1.re.x[e] = lanes::lane_value(rw, e);
+            p1.im.x[e] = lanes::lane_value(rw, P + e);
+            p2.x[e] = lanes::lane_value(rw, 2 * P + e);
+            bt.x[e] = lanes::lane_value(rw, 3 * P + e);
+        }
+        if (is_zero(bt)) continue;  // identity reflector
+        CAcc<P> t = cacc_from(cmul(p1, sld(jj)));
         acc_fma(t.re, p2, D.re);
         acc_fma(t.im, p2, D.im);
         const CV<P> sc = cacc_get(t);  // p1 a_j + p2 D
@@ -631,7 +665,7 @@ __global__ __launch_bounds__(kThreads) void k_cpanel(CPersistArgs g)
         const int i = tid + q * kThreads;
         if (i > jc && i < h) {
             const CV<P> x = sld(i);
-            cst_coherent(xc, g.xps, i, x);
+            cst_coherent(xc, g.xps, i, cword_full(x));
             acc_fma(sacc, x.re, x.re);
             acc_fma(sacc, x.im, x.im);
         }
@@ -693,9 +727,6 @@ __global__ __launch_bounds__(kThreads) void k_cpanel(CPersistArgs g)
         }
         stm(g.beta, g.bps, c, bt);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    if (tid == 0) __hip_atomic_store(g.count, (unsigned)(c + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // ---- final values (read only by later launches): row j of step j, R_cc, v = x/v1 below
 #pragma unroll
@@ -730,6 +761,13 @@ __global__ __launch_bounds__(kThreads) void k_cpanel(CPersistArgs g)
 }
 
 namespace {
+// The hand-off words of a k_cpanel launch: n1 at a, n2 at b
+__global__ __launch_bounds__(kThreads) void k_cpanel_init(unsigned long long *a, long n1, unsigned long long *b, long n2)
+{
+    for (long i = (long)blockIdx.x * kThreads + threadIdx.x; i < n1 + n2; i += (long)gridDim.x * kThreads)
+        (i < n1 ? a[i] : b[i - n1]) = kTrEmpty;
+}
+
 // A wait of the persistent panel timed out: R(0, 0) := NaN, so that the failure shows.
 __global__ void k_cpoison(const int *err, double *A)
 {
@@ -1070,8 +1108,8 @@ template <int P>
 constexpr int kCInvCols = 1;
 
 struct CLayout {
-    size_t beta, T, G, S, U, y, ctr, px, pr, total;  // ctr, px, pr: the persistent panel's count and
-                                                     // error flag, staged columns, scalars
+    size_t beta, T, G, S, U, y, ctr, px, pr, total;  // ctr, px, pr: the persistent panel's error flag,
+                                                     // staged columns, scalars
     int sc;  // columns of S and U
 };
 
@@ -1092,7 +1130,7 @@ inline CLayout clayout(int P, int m, int n, int tile)
     L.S = take(sizeof(double) * 2 * (size_t)P * tile * L.sc);
     L.U = take(sizeof(double) * 2 * (size_t)P * tile * L.sc);
     L.y = take(sizeof(double) * 2 * (size_t)P * (m > n ? m : n));
-    L.ctr = take(sizeof(unsigned) * 2);
+    L.ctr = take(sizeof(int));
     L.px = take(sizeof(double) * 2 * (size_t)P * m * tile);
     L.pr = take(sizeof(double) * 4 * (size_t)P * n);
     L.total = off;
@@ -1201,15 +1239,16 @@ int cqr_t(int m, int n, int tile, double *A, int lda, double *T, int ldt, void *
     const long psa = (long)lda * n, tps = (long)ldt * n, gps = (long)tile * tile, sps = (long)tile * L.sc;
     const int N = n / tile;
     const CPanelArgs pa{A, (long)lda, psa, m, 0, 0, beta, (long)n};
-    unsigned *count = (unsigned *)(w + L.ctr);
-    int *err = (int *)(count + 1);
-    // each panel as one persistent launch (the default for qd and od, where it is the faster
-    // form; measured on MI355X: dd and double are faster a launch per column) while its column
-    // fits and its workgroups can all be resident, else a launch per column
+    int *err = (int *)(w + L.ctr);
+    // each panel as one persistent launch while its column fits and its workgroups can all be
+    // resident, else a launch per column.  Measured, persistent against a launch per column (csolve): dd 64
+    // 549 against 614 us, 512 3.69 / 4.59 ms, 2000 x 64 0.79 / 1.31 ms; qd 64 1.84 / 2.47, 512 15.2 / 20.9 ms;
+    // double 1024 x 512 2.82 / 3.00, 4000 x 64 0.64 / 1.28, 512 2.55 / 2.61 ms, but 64 347 / 331 us: a
+    // double column of up to 256 rows is one row a thread, and the launch no slower than the hand-off
     const Tuning tu = tuning();
-    const bool use = tu.cpanel == 1 || (tu.cpanel == 2 && P >= 4);
+    const bool use = tu.cpanel == 1 || (tu.cpanel == 2 && (P >= 2 || m > kThreads));
     const bool fits = use && cpanel_capacity<P>() >= tile;
-    MDLS_LAUNCH("k_zero", P, 0, k_zero_u32, dim3(1), dim3(64), s, count, 2);
+    MDLS_LAUNCH("k_zero", P, 0, k_zero_u32, dim3(1), dim3(64), s, (unsigned *)err, 1);
     bool persisted = false;
     for (int k = 0; k < N; ++k) {
         const int kt = k * tile, jend = kt + tile;
@@ -1217,7 +1256,11 @@ int cqr_t(int m, int n, int tile, double *A, int lda, double *T, int ldt, void *
         const bool done = fits && h <= kCPanelRows<P>;
         if (done) {
             const CPersistArgs ca{A, (long)lda, psa, m, kt, beta, (long)n, (double *)(w + L.px), (long)m * tile,
-                                  (double *)(w + L.pr), count, err, tu.spin_limit};
+                                  (double *)(w + L.pr), err, tu.spin_limit};
+            const long nx = 2L * P * m * tile, nr = 4L * P * tile;
+            MDLS_LAUNCH("k_cpanel_init", P, 0, k_cpanel_init, dim3((unsigned)std::min((nx + kThreads * 4 - 1) / (kThreads * 4), 512L)),
+                        dim3(kThreads), s, (unsigned long long *)ca.xs, nx,
+                        (unsigned long long *)(ca.rec + 4L * P * kt), nr);
             double work = 0;
             for (int j = 0; j < tile; ++j) work += 8.0 * (h - j) * (tile - j - 1) + 6.0 * (h - j);
             MDLS_LAUNCH_SHM("k_cpanel", P, work, (k_cpanel<P>), dim3(tile), dim3(kThreads),
@@ -1373,7 +1416,7 @@ int csolve_t(int m, int n, int tile, double *A, int lda, double *b, double *x, v
     MDLS_LAUNCH("k_copy", P, 0, k_copy, dim3((n + 255) / 256), dim3(256), s, b, (long)m, y, (long)n, n, 2 * P);
     cbacksub_tiles<P>(L, w, n, tile, A, lda, (long)lda * n, y, x, n, d_info, s);
     // a timed-out wait of a persistent panel (cqr_t clears the flag first)
-    MDLS_LAUNCH("k_fold_err", P, 0, k_fold_err, dim3(1), dim3(64), s, (const int *)(w + L.ctr) + 1, d_info);
+    MDLS_LAUNCH("k_fold_err", P, 0, k_fold_err, dim3(1), dim3(64), s, (const int *)(w + L.ctr), d_info);
     return hipGetLastError() == hipSuccess ? 0 : MDLS_EHIP;
 }
 

@@ -354,7 +354,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
         return gv;
     };
     // lane l < jj: w_l = sum_{l <= k < jj} T(l, k) g(k, jj).  W <= 8: a lane forms one product (l = lane / W,
-    // k = lane % W) and the W lanes of an l are summed (od n = 1024: SOMETHING); W = 16: lane l
+    // k = lane % W) and the W lanes of an l are summed (n = 1024: qd 11.42 -> 11.14 ms, od 54.2 -> 53.6); W = 16: lane l
     // sums, even and odd k in two accumulators, so the two halves of the sum overlap
     auto t_w = [&](int jj, const V<P> &gv) __attribute__((always_inline)) {
         Acc<P> w0 = acc_zero<P>();
@@ -676,11 +676,11 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
         if (wid == 0) {
             if (!zs && spread) {
                 if constexpr (P >= 8) {
-                    constexpr int L = lanes::kDigits<P>;
-                    const double X1 = lanes::digits<P, P>(x1.x, pe, lane);
+                    constexpr int L = lanes::kDigits;
+                    const double X1 = lanes::digits<P>(x1.x, pe, lane);
                     const double Q = lanes::carry(
-                        lanes::mul<L>(X1, X1, lane) + lanes::digits<P, P>(sig.x, 2 * pe, lane), lane);
-                    const double Y = lanes::rsqrt<P>(Q, __builtin_ldexp(q0, -2 * pe), lane);
+                        lanes::mul<L>(X1, X1, lane) + lanes::digits<P>(sig.x, 2 * pe, lane), lane);
+                    const double Y = lanes::rsqrt(Q, __builtin_ldexp(q0, -2 * pe), lane);
                     const double S = lanes::mul<L>(Q, Y, lane);
                     lds.dig[0][lane] = S;
                     const V<P> m = lanes::limbs<P>(S, pe), im = lanes::limbs<P>(Y, -pe);
@@ -703,7 +703,7 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
             if (!zs && (pos || !small)) {
                 if (spread) {
                     if constexpr (P >= 8)
-                        lds.dig[1][lane] = lanes::recip<P>(lanes::digits<P, P>(sig.x, se, lane),
+                        lds.dig[1][lane] = lanes::recip(lanes::digits<P>(sig.x, se, lane),
                                                            __builtin_ldexp(sig.x[0], -se), lane);
                 } else {
                     const V<P> is = recip(sig);
@@ -726,14 +726,14 @@ __device__ __forceinline__ void panel_run(const PanelArgs &g, int bid, PanelLds<
             if (!zs) {
                 if (spread) {
                     if constexpr (P >= 8) {
-                        const double S = lds.dig[0][lane], X1 = lanes::digits<P, P>(x1.x, pe, lane);
+                        const double S = lds.dig[0][lane], X1 = lanes::digits<P>(x1.x, pe, lane);
                         if (!pos && small) {
                             const double D = lanes::carry(S - X1, lane);  // mu - x1, in [1, 4)
                             const double d0 = __builtin_ldexp(s_mu[0] - x1.x[0], -pe);
-                            rho = lanes::limbs<P>(-lanes::recip<P>(D, d0, lane), -pe);
+                            rho = lanes::limbs<P>(-lanes::recip(D, d0, lane), -pe);
                         } else {
                             const double F = lanes::carry(S + X1, lane);
-                            rho = lanes::limbs<P>(-lanes::mul<lanes::kDigits<P>>(F, lds.dig[1][lane], lane), pe - se);
+                            rho = lanes::limbs<P>(-lanes::mul<lanes::kDigits>(F, lds.dig[1][lane], lane), pe - se);
                         }
                     }
                 } else {
