@@ -31,12 +31,12 @@
  * NaN and Inf in the input propagate to the output unchecked (d_info stays 0 unless R(k,k) is
  * exactly zero).  No call throws.
  *
- * Co-residency: a Householder panel of more than one workgroup synchronises its workgroups
- * once per column with a grid barrier, so all of them must be resident at once.  The library
+ * Co-residency: a Householder panel of more than one workgroup exchanges its workgroups' sums
+ * once per column, each waiting for the others', so all of them must be resident at once.  The library
  * checks that the panel's workgroups fit the device (occupancy x compute units) and otherwise
  * returns MDLS_EUNSUPPORTED; the concurrent trailing update never waits, so it cannot block
- * them.  Work of other processes or streams that holds compute units for longer than the
- * barrier's spin limit (about 0.1 s by default) can still make a barrier give up: it then
+ * them, and a back substitution's workgroup waits only for those dispatched before it.  Work of other processes or streams that holds compute units for longer than the
+ * waits' spin limit (about 0.1 s by default) can still make a wait give up: it then
  * lets its workgroup continue, every kernel exits normally, and *d_info reports -1.
  *
  * Threading: calls on distinct streams with distinct buffers and workspaces may run
@@ -78,16 +78,20 @@ int mdls_finalize(void);
  * rounding of the update products; the complex reflector's formulas); the others change only
  * speed or, for the spin limit, how long a grid barrier (or the complex panel's wait for the
  * previous column) polls before it reports -1 through *d_info.
- *   MDLS_TUNE_LOOKAHEAD        1 (default): concurrent trailing update after mdls_init; 0: off
+ *   MDLS_TUNE_LOOKAHEAD        1 (default): concurrent trailing update on the side stream after
+ *                              mdls_init; 0: off.  Double, dd and qd factorisations of up to 4096 /
+ *                              4096 / 2048 rows hold it in the panel's own launch and use no side
+ *                              stream (except with the alternative panel shape or the split update)
  *   MDLS_TUNE_PANEL_VARIANT    0 (default) or 1: the panel kernel's alternative shape (more rows
  *                              per thread: dd 512 x 8, qd 256 x 4, od 256 x 2 threads x rows);
  *                              octo-double factorisations of more than 1024 rows use the
  *                              alternative shape under either value
- *   MDLS_TUNE_APPLY_GRID_CAP   workgroups of the concurrent trailing update; 0 (default): 448
- *                              (two per CU on 224 CUs), for od 224 once fewer than
- *                              MDLS_TUNE_APPLY_WIDE_ROWS (default 768) rows remain
- *   MDLS_TUNE_SPIN_LIMIT       polls (each after a sleep of about 64 cycles) before a grid
- *                              barrier gives up; default 2^22
+ *   MDLS_TUNE_APPLY_GRID_CAP   workgroups of the concurrent trailing update; 0 (default): on the
+ *                              side stream 448 (two per CU on 224 CUs), for od 224 once fewer than
+ *                              MDLS_TUNE_APPLY_WIDE_ROWS (default 768) rows remain; in the panel's
+ *                              launch one per group of columns
+ *   MDLS_TUNE_SPIN_LIMIT       polls (each after a sleep of about 64 cycles) before a wait of one
+ *                              workgroup for another gives up; default 2^22
  *   MDLS_TUNE_SPLIT_UPDATE     0 (default) or 1: mdls_solve_refined's double-double factorisation
  *                              forms its trailing-update products Y^T C on the FP64 matrix cores
  *                              by exact slicing (the product of mdls_dd_gemm_tn method 1) instead
@@ -186,8 +190,9 @@ int mdls_form_w(int p, int m, int n, int tile, const double *A, int lda, const d
  * triangular U and b; output x with U x = b): solves R x = y with R the upper triangle of
  * the leading n x n block of R (ldr >= n, entries below the diagonal are not read), n a
  * multiple of tile.  x holds y on entry (P planes of n doubles) and the solution on exit.
- * Stage 1 inverts the n/tile diagonal tiles, stage 2 alternates x_i := U_i^{-1} b_i with
- * b_j -= A_{j,i} x_i for j < i.  *d_info: 0, or k > 0 for the first exactly zero R(k,k).
+ * One launch works in blocks of 32 rows, whatever the tile: each block's workgroup inverts its
+ * diagonal block and takes b_j -= A_{j,i} x_i as the blocks below publish their x_i.  *d_info: 0;
+ * k > 0 for the first exactly zero R(k,k); -1 if a wait gave up.
  */
 int mdls_backsub(int p, int n, int tile, const double *R, int ldr, double *x, void *ws,
                  size_t ws_bytes, int *d_info, hipStream_t stream);

@@ -8,16 +8,20 @@
 //                 choice), the in-panel reflector updates, and the panel's compact-WY factor T
 //                 (H_0 ... H_{W-1} = I - Y T Y^T, so the paper's W = -Y T).  The panel's rows
 //                 stay in registers across all its columns; one workgroup reduction (and, when
-//                 the panel spans several workgroups, one grid barrier) per column.
+//                 the panel spans several workgroups, one exchange of tagged words) per column.
+//     k_step   -- a panel and the previous panel's trailing update in one launch (double, dd and
+//                 qd while their rows fit); elsewhere the update is
 //     k_apply_s, k_apply_t, k_apply_u -- the trailing update C := C + Y (W^T C) =
 //                 C - Y T^T (Y^T C) (paper's "YWT*C" and "R + YWTC" fused), applied to every
 //                 column right of the panel and to the right-hand side, so Q^T b comes out of
 //                 the factorisation.
 //   Back substitution (Section 2, Algorithm 1):
-//     k_invert -- invert the diagonal tiles (all columns of a tile in parallel, one row step at
-//                 a time);
-//     k_bs_xi  -- x_i := U_i^{-1} b_i;
-//     k_bs_upd -- b_j -= A_{j,i} x_i for every j < i at once.
+//     k_trsv   -- one launch, a workgroup per block of rows: its diagonal block inverted, the x of
+//                 the blocks below taken as they are published, b_j -= A_{j,i} x_i, x_j := U_j^{-1} b_j;
+//     k_invert, k_inv_blocks, k_bs_xi, k_bs_upd -- the refined solve's, whose corrections use the
+//                 diagonal tiles' inverses again: the inverses, then per tile x_i := U_i^{-1} b_i and
+//                 b_j -= A_{j,i} x_i for every j < i at once.
+//   Q^T B and Q B: k_gemm, k_trmm_v and k_nn_sub_v, in blocks of outputs.
 //
 // Multiple-double numbers are P limb planes (limb 0 most significant); see md.hpp for the
 // arithmetic.
