@@ -427,7 +427,7 @@ __global__ __launch_bounds__(kThreads) void k_cstep_r(CPanelArgs g)
 // arithmetic makes, a reader polls what it needs until none is left, and x is taken before the
 // scalars.  So there is no counter, no fence and no acquire between two columns, and a reader
 // forms D while the owner still reduces sigma and forms the reflector.  What bounds a column is
-// that chain of two reductions, the reflector and two hand-offs: dd 512, tile 128, 3.9 us (csolve 4.27 ms a
+// that chain of two reductions, the reflector and two hand-offs: dd 512, tile 128, 3.9 us (csolve then 4.27 ms a
 // launch per column, 3.36 here).  The same with the counter and fences before: csolve dd 512 (tile 32)
 // 4.88 -> 3.69 ms, qd 512 19.4 -> 15.2, od 192 34.3 -> 27.1 ms.  A workgroup waits
 // only for lower-numbered ones and each wait is a bounded poll (a time-out raises *err, after
@@ -1004,14 +1004,14 @@ __global__ __launch_bounds__(kThreads) void k_ctn(const double *Y, long lda, lon
 
 // U = T^H S (H: U(i, c) = sum_{l <= i} conj(T(l, i)) S(l, c)) or U = T S (for Q B: sum_{l >= i} T(i, l) S(l, c)).
 // Lane i of a wave forms row i, the waves every fourth l: bound by the serial sum of a row, a quarter as long so
-// (dd 512, tile 128: 41 -> 29.5 us a launch).
+// (dd 512, tile 128: 41 -> 23 us a launch).
 template <int P, bool H>
 __global__ __launch_bounds__(kThreads) void k_ctrmm(const double *T, long ldt, long tps, const double *S, long sps,
                                                    double *U, int tile)
 {
     constexpr int NW = kThreads / 64;
     __shared__ double sp[(NW - 1) * 64 * 2 * P];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i = blockIdx.x * 64 + lane, c = blockIdx.y;
     CAcc<P> acc = cacc_zero<P>();
     if (i < tile) {
@@ -1045,18 +1045,38 @@ __global__ void k_cidentity(double *B, long ldb, long bps, int rows, int cols, i
 }
 }  // namespace
 
-// B(r, c) -= sum_l Y(r, l) U(l, c), r < h
+// B(r, c) -= sum_l Y(r, l) U(l, c), r < h.  Lane r of a wave forms row r, the waves every fourth l (as in k_ctrmm; the
+// wave's index is uniform, so the entries of U are scalar loads).  Bound by FP64 issue where the grid fills the
+// chip, by the serial sum of a row where it does not: csolve dd 512, tile 128, 58 -> 28 us a launch; wide products
+// (Q^H A, dd 2048 x 1024 10.9 -> 10.4 ms) within 5% either way.
 template <int P>
 __global__ __launch_bounds__(kThreads) void k_cnn_sub(const double *Y, long lda, long ps, int h, int tile, const double *U,
                                                      long ups, double *B, long ldb, long bps)
 {
-    const long r = (long)blockIdx.x * kThreads + threadIdx.x;
+    constexpr int NW = kThreads / 64;
+    __shared__ double sp[(NW - 1) * 64 * 2 * P];
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long r = (long)blockIdx.x * 64 + lane;
     const int c = blockIdx.y;
-    if (r >= h) return;
-    CAcc<P> acc = cacc_from(cldm<P>(B, bps, (long)c * ldb + r));
-    const int lmax = (r < tile - 1) ? (int)r : tile - 1;
-    for (int l = 0; l <= lmax; ++l)
-        cacc_fma_step<P, false>(acc, cneg(cy_entry<P>(Y, lda, ps, r, l, h, tile)), cldm<P>(U, ups, (long)c * tile + l), l);
+    CAcc<P> acc = cacc_zero<P>();
+    if (r < h) {
+        if (wid == 0) acc = cacc_from(cldm<P>(B, bps, (long)c * ldb + r));
+        const int lmax = (r < tile - 1) ? (int)r : tile - 1;
+        int nt = 0;
+        for (int l = wid; l <= lmax; l += NW)
+            cacc_fma_step<P, false>(acc, cneg(cy_entry<P>(Y, lda, ps, r, l, h, tile)), cldm<P>(U, ups, (long)c * tile + l), nt++);
+    }
+    const CV<P> v = cacc_get(acc);
+    if (wid > 0) clds_st(&sp[((wid - 1) * 64 + lane) * 2 * P], v);
+    __syncthreads();
+    if (wid > 0 || r >= h) return;
+    acc = cacc_from(v);
+#pragma unroll
+    for (int k = 0; k < NW - 1; ++k) {
+        const CV<P> o = clds_ld<P>(&sp[(k * 64 + lane) * 2 * P]);
+        acc_add(acc.re, o.re);
+        acc_add(acc.im, o.im);
+    }
     cstm(B, bps, (long)c * ldb + r, cacc_get(acc));
 }
 
@@ -1192,8 +1212,8 @@ void cblock_apply_h(const double *Y, long lda, long psa, int h, int tile, const 
                 tile, B, ldb, bps, nc, S, sps);
     MDLS_LAUNCH("k_ctrmm_h", P, 2.0 * tile * tile * nc, (k_ctrmm<P, true>), dim3((tile + 63) / 64, nc),
                 dim3(kThreads), s, Tk, ldt, tps, S, sps, U, tile);
-    MDLS_LAUNCH("k_cnn_sub", P, 4.0 * h * tile * nc, (k_cnn_sub<P>), dim3((h + kThreads - 1) / kThreads, nc),
-                dim3(kThreads), s, Y, lda, psa, h, tile, U, sps, B, ldb, bps);
+    MDLS_LAUNCH("k_cnn_sub", P, 4.0 * h * tile * nc, (k_cnn_sub<P>), dim3((h + 63) / 64, nc), dim3(kThreads), s, Y, lda, psa,
+                h, tile, U, sps, B, ldb, bps);
 }
 
 // The panel's columns kt .. jend - 1 a launch at a time: the first column's reflector, then per
@@ -1248,10 +1268,11 @@ int cqr_t(int m, int n, int tile, double *A, int lda, double *T, int ldt, void *
     // each panel as one persistent launch while its column fits and its workgroups can all be
     // resident, else a launch per column.  Measured, persistent against a launch per column (csolve): dd 64
     // 549 against 614 us, 512 3.69 / 4.59 ms, 2000 x 64 0.79 / 1.31 ms; qd 64 1.84 / 2.47, 512 15.2 / 20.9 ms;
-    // double 1024 x 512 2.82 / 3.00, 4000 x 64 0.64 / 1.28, 512 2.55 / 2.61 ms, but 64 347 / 331 us: a
-    // double column of up to 256 rows is one row a thread, and the launch no slower than the hand-off
+    // double (tile 32 and 64) 1024 x 512 2.82 / 3.00, 4000 x 64 0.64 / 1.28, 512 2.55 / 2.61 ms, but 64 347 /
+    // 331 us and (QR, tile 8) 1024 7.54 / 7.25 ms: a double column of up to 256 rows is one row a thread and a
+    // launch no slower than the hand-off, and a narrow panel's few launches weigh no more than its own two
     const Tuning tu = tuning();
-    const bool use = tu.cpanel == 1 || (tu.cpanel == 2 && (P >= 2 || m > kThreads));
+    const bool use = tu.cpanel == 1 || (tu.cpanel == 2 && (P >= 2 || (m > kThreads && tile >= 32)));
     const bool fits = use && cpanel_capacity<P>() >= tile;
     MDLS_LAUNCH("k_zero", P, 0, k_zero_u32, dim3(1), dim3(64), s, (unsigned *)err, 1);
     bool persisted = false;
@@ -1343,8 +1364,8 @@ int capply_q_t(int m, int n, int tile, const double *A, int lda, const double *T
                         (long)lda, psa, h, tile, Bc + kt, (long)ldb, bps, nc, S, sps);
             MDLS_LAUNCH("k_ctrmm_n", P, 2.0 * tile * tile * nc, (k_ctrmm<P, false>), dim3((tile + 63) / 64, nc),
                         dim3(kThreads), s, T + kt * ldt, (long)ldt, tps, S, sps, U, tile);
-            MDLS_LAUNCH("k_cnn_sub", P, 4.0 * h * tile * nc, (k_cnn_sub<P>), dim3((h + kThreads - 1) / kThreads, nc),
-                        dim3(kThreads), s, Y, (long)lda, psa, h, tile, U, sps, Bc + kt, (long)ldb, bps);
+            MDLS_LAUNCH("k_cnn_sub", P, 4.0 * h * tile * nc, (k_cnn_sub<P>), dim3((h + 63) / 64, nc), dim3(kThreads), s, Y,
+                        (long)lda, psa, h, tile, U, sps, Bc + kt, (long)ldb, bps);
         }
     }
     return hipGetLastError() == hipSuccess ? 0 : MDLS_EHIP;
