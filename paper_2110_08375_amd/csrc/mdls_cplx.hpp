@@ -427,8 +427,8 @@ __global__ __launch_bounds__(kThreads) void k_cstep_r(CPanelArgs g)
 // arithmetic makes, a reader polls what it needs until none is left, and x is taken before the
 // scalars.  So there is no counter, no fence and no acquire between two columns, and a reader
 // forms D while the owner still reduces sigma and forms the reflector.  What bounds a column is
-// that chain of two reductions, the reflector and two hand-offs: dd 512, tile 128, 3.9 us (csolve then 4.27 ms a
-// launch per column, 3.36 here).  The same with the counter and fences before: csolve dd 512 (tile 32)
+// that chain of two reductions, the reflector and two hand-offs: dd 512, tile 128, 3.9 us (csolve
+// 3.36 ms, a launch per column 4.27).  The same with the counter and fences before: csolve dd 512 (tile 32)
 // 4.88 -> 3.69 ms, qd 512 19.4 -> 15.2, od 192 34.3 -> 27.1 ms.  A workgroup waits
 // only for lower-numbered ones and each wait is a bounded poll (a time-out raises *err, after
 // which no wait polls for long), so the grid always drains.

@@ -21,7 +21,7 @@ def M():
 
 @pytest.mark.parametrize("P,m,n,tile", [
     (2, 9, 8, 8), (2, 255, 32, 16), (2, 256, 32, 32), (2, 257, 24, 8), (2, 2048, 16, 8), (2, 2052, 16, 8),
-    (2, 256, 256, 256), (1, 256, 32, 16), (1, 257, 32, 16), (1, 4100, 16, 8), (4, 1024, 16, 8), (4, 257, 16, 16),
+    (2, 256, 256, 256), (1, 256, 64, 32), (1, 257, 64, 32), (1, 257, 32, 16), (1, 4100, 16, 8), (4, 1024, 16, 8), (4, 257, 16, 16),
     (8, 512, 8, 8),
 ])
 def test_cpanel_edges(M, orc, P, m, n, tile):
