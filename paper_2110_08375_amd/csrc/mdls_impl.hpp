@@ -1470,8 +1470,8 @@ __global__ __launch_bounds__(NT) void k_batch(BatchArgs g)
 #pragma unroll
                     for (int k = 0; k < P; ++k) sY[(i * P + k) * kBatchRows + r] = y.x[k];
                 }
-                __syncthreads();
             }
+            __syncthreads();  // sY, and of a workgroup alone T's last column, which one wave stored last
             batch_update<P, W, NT, STAGED>(pa.A, lda, ps, pa.h, pa.wact, pa.T, A + (long)(c0 + pa.wact) * lda + c0,
                                            d.n - c0 - pa.wact, bp + c0, d.m, mem * NW + wid, team * NW, sY);
             __syncthreads();

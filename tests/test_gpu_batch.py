@@ -235,3 +235,24 @@ def test_batched_team_plans(M, orc, P, count, m_lo, m_hi):
             err = md_err(x_of(M, descs, xg, P, k), mdgen.md_ones(P, n))
             assert err <= TOL[P] * max(1.0, kap[k]), (v, k, m, n, err, kap[k])
             assert err <= 64 * n * unit(P) * max(1.0, kap[k]), (v, k, m, n, err, kap[k])
+
+
+@pytest.mark.parametrize("P", (2, 4))
+def test_batched_single_workgroup_problems_repeat(M, orc, P):
+    """512 equal problems, which all stay on one workgroup each, in every kernel variant (the ones that
+    keep the panel in LDS for the update and the one that does not): T's last column is stored by
+    one wave and read by all, so three runs give the same bits, and x matches the oracle."""
+    shapes = [(37, 29)] * 512
+    print("case batched single P=%d" % P, flush=True)
+    descs, A, b, x_len, mats = make_batch(M, P, shapes, 1700, lambda k, Ak: orc.rhs_for(Ak, mdgen.md_ones(P, Ak.shape[1])))
+    kap = [float(np.linalg.cond(Ak[0].T)) for Ak, _ in mats]
+    ws = M.batch_workspace(P, len(shapes), dev())
+    M.batch_plan(P, descs, ws)
+    for v in range(M.batch_variants(P)):
+        xg, info = run_batch(M, P, descs, A, b, x_len, v, ws)
+        assert np.all(info == 0), v
+        for k, (m, n) in enumerate(shapes):
+            err = md_err(x_of(M, descs, xg, P, k), mdgen.md_ones(P, n))
+            assert err <= 64 * n * unit(P) * max(1.0, kap[k]), (v, k, m, n, err, kap[k])
+        for _ in range(2):
+            assert np.array_equal(run_batch(M, P, descs, A, b, x_len, v, ws)[0], xg), v
