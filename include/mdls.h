@@ -35,9 +35,10 @@
  * once per column, each waiting for the others', so all of them must be resident at once.  The library
  * checks that the panel's workgroups fit the device (occupancy x compute units) and otherwise
  * returns MDLS_EUNSUPPORTED; the concurrent trailing update never waits, so it cannot block
- * them, and a back substitution's workgroup waits only for those dispatched before it.  Work of other processes or streams that holds compute units for longer than the
- * waits' spin limit (about 0.1 s by default) can still make a wait give up: it then
- * lets its workgroup continue, every kernel exits normally, and *d_info reports -1.
+ * them, and a back substitution's workgroup waits only for those dispatched before it.  Work of
+ * other processes or streams that holds compute units for longer than the waits' spin limit (0.8 s
+ * by default, MDLS_TUNE_SPIN_LIMIT) can still make a wait give up: it then lets its workgroup
+ * continue, every kernel exits normally, and *d_info reports -1.
  *
  * Threading: calls on distinct streams with distinct buffers and workspaces may run
  * concurrently.  One workspace must not be used by two calls in flight at once.
@@ -90,8 +91,13 @@ int mdls_finalize(void);
  *                              side stream 448 (two per CU on 224 CUs), for od 224 once fewer than
  *                              MDLS_TUNE_APPLY_WIDE_ROWS (default 768) rows remain; in the panel's
  *                              launch one per group of columns
- *   MDLS_TUNE_SPIN_LIMIT       polls (each after a sleep of about 64 cycles) before a wait of one
- *                              workgroup for another gives up; default 2^22
+ *   MDLS_TUNE_SPIN_LIMIT       polls before a wait of one workgroup for another gives up; default
+ *                              2^22.  A poll takes 0.18 us on an idle device, with or without the
+ *                              sleep of 64 cycles that some waits put between two (0.8 s in all);
+ *                              a back substitution's workgroup whose turn is far off sleeps 8 or 64
+ *                              times as long (1.7 and 8 s).  A batch's teams meet under a limit of
+ *                              at least 2^24 polls whatever this one is, since their first members
+ *                              wait for the end of other problems
  *   MDLS_TUNE_SPLIT_UPDATE     0 (default) or 1: mdls_solve_refined's double-double factorisation
  *                              forms its trailing-update products Y^T C on the FP64 matrix cores
  *                              by exact slicing (the product of mdls_dd_gemm_tn method 1) instead

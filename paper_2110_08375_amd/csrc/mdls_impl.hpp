@@ -1278,6 +1278,11 @@ __global__ __launch_bounds__(NT, 2) void k_step(StepArgs g)
 constexpr int kBatchRows = 512;
 constexpr int kTeamMax = 16;      // most workgroups on one problem
 constexpr int kTeamCtrs = 1;      // a team's barrier counter
+// Polls before a team's first barrier gives up, at least: its members take their slots one after the
+// other as workgroups come free, so the first of them waits for the end of another problem (0.13 s for
+// qd 512 x 512 on one workgroup) and not, as every later wait, for a workgroup that is running beside it.
+// A poll takes 0.19 us on an idle device, so this is 3 s.
+constexpr unsigned kTeamPolls = 1u << 24;
 
 struct BatchDesc {
     int m, n;
@@ -1425,7 +1430,7 @@ __global__ __launch_bounds__(NT) void k_batch(BatchArgs g)
             if (team > 1) {
                 __syncthreads();
                 ++nsync;
-                if (wid == 0) grid_sync(ctr, nsync * (unsigned)team, g.err, g.spin);
+                if (wid == 0) grid_sync(ctr, nsync * (unsigned)team, g.err, nsync > 1 ? g.spin : max(g.spin, kTeamPolls));
                 __syncthreads();
             }
         };
@@ -3486,8 +3491,7 @@ inline BatchCost batch_cost(int P, const BatchDesc &d)
 // Teams may stand anywhere in the list: slots are taken in order, so at any time at most one team
 // is incomplete, its waiting members are fewer than the resident workgroups, and every complete
 // team finishes without waiting for a later slot.  The members that come first wait until a running
-// problem ends, at most about 0.13 s (qd 512 x 512 on one workgroup); the barrier's default spin
-// limit is some seconds of polls.
+// problem ends, which the limit on the waits inside a team does not count (kTeamPolls).
 // Returns the slot list (problem index in the sorted plan * kTeamMax + member).
 inline std::vector<int> batch_schedule(int P, std::vector<BatchDesc> &plan)
 {

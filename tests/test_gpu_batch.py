@@ -256,3 +256,27 @@ def test_batched_single_workgroup_problems_repeat(M, orc, P):
             assert err <= 64 * n * unit(P) * max(1.0, kap[k]), (v, k, m, n, err, kap[k])
         for _ in range(2):
             assert np.array_equal(run_batch(M, P, descs, A, b, x_len, v, ws)[0], xg), v
+
+
+def test_batched_teams_meet_under_a_low_spin_limit(M):
+    """More workgroups in teams than the device holds: a team's first members wait for the end of
+    other problems (milliseconds).  A spin limit of 20000 polls (about 4 ms), ample for the waits
+    inside a team, does not end that wait: every problem is solved, bit for bit as under the default."""
+    from paper_2110_08375_amd import mdls
+
+    P = 4
+    shapes = [(512, 512)] * 24 + mdgen.batch_shapes(136, 5, m_lo=300, m_hi=512, n_lo=250)
+    descs, A, b, x_len, _ = make_batch(M, P, shapes, 2500, lambda k, Ak: mdgen.md_vector(P, Ak.shape[2], 3 + k, 3))
+    ws = M.batch_workspace(P, len(shapes), dev())
+    M.batch_plan(P, descs, ws)
+    print("case batched low spin limit", flush=True)
+    xg, info = run_batch(M, P, descs, A, b, x_len, 1, ws)
+    assert np.all(info == 0)
+    saved = M.get_tuning(mdls.MDLS_TUNE_SPIN_LIMIT)
+    M.set_tuning(mdls.MDLS_TUNE_SPIN_LIMIT, 20000)
+    try:
+        xl, info = run_batch(M, P, descs, A, b, x_len, 1, ws)
+    finally:
+        M.set_tuning(mdls.MDLS_TUNE_SPIN_LIMIT, saved)
+    assert np.all(info == 0), "%d problems report %s" % ((info != 0).sum(), set(info.tolist()))
+    assert np.array_equal(xl, xg)
