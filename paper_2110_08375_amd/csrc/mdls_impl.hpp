@@ -2154,11 +2154,13 @@ __global__ __launch_bounds__(kTrNT, 2) void k_trsv(TrsvArgs g)
         for (int w = 0; w < P; ++w) ok = ok && wd[w] != kTrEmpty;
         return ok;
     };
-    // after a failed poll: whether to give up
+    // after a failed poll: whether to give up.  Who gives up writes the status: its x carries no order, so no
+    // other workgroup that has taken it can be sure to see *err.
     auto give_up = [&](unsigned &spins) __attribute__((always_inline)) {
         if ((spins & 255u) == 255u && __hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return true;
         if (++spins > g.spin) {
             __hip_atomic_store(g.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(g.d_info, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return true;
         }
         return false;
@@ -2340,7 +2342,7 @@ __global__ __launch_bounds__(kTrNT, 2) void k_trsv(TrsvArgs g)
         }
         __syncthreads();  // lds.v is written again
     }
-    // the workgroup of the first rows is the last to finish: it has waited for all the others
+    // a wait that gave up before this launch (the factorisation's)
     if (j == 0 && tid == 0 && __hip_atomic_load(g.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) *g.d_info = -1;
 }
 

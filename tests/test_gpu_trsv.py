@@ -79,3 +79,26 @@ def test_trsv_status():
         M.set_tuning(mdls.MDLS_TUNE_SPIN_LIMIT, saved)
     _, info = M.backsub(2, Ug, torch.from_numpy(y).cuda(), 1)
     assert int(info.item()) == 0
+
+
+@pytest.mark.parametrize("P,n", [(1, 1500), (2, 200), (2, 1500), (4, 900), (8, 1100)])
+def test_trsv_status_of_a_wait_that_gave_up(P, n):
+    """With a spin limit of 0 or 2 polls waits give up or not as the workgroups happen to run: x is then
+    either the solution or *info is -1, in each of ten runs."""
+    import paper_2110_08375_amd as M
+    from paper_2110_08375_amd import mdls
+
+    print("case trsv status P=%d n=%d" % (P, n), flush=True)
+    U, _, y = problem(P, n, n)
+    Ug, yg = torch.from_numpy(U).cuda(), torch.from_numpy(y).cuda()
+    ref, info = M.backsub(P, Ug, yg.clone(), 1)
+    assert int(info.item()) == 0
+    saved = M.get_tuning(mdls.MDLS_TUNE_SPIN_LIMIT)
+    try:
+        for rep in range(10):
+            M.set_tuning(mdls.MDLS_TUNE_SPIN_LIMIT, 2 * (rep % 2))
+            x, info = M.backsub(P, Ug, yg.clone(), 1)
+            assert int(info.item()) in (0, -1)
+            assert int(info.item()) == -1 or torch.equal(x, ref), rep
+    finally:
+        M.set_tuning(mdls.MDLS_TUNE_SPIN_LIMIT, saved)
