@@ -2236,10 +2236,12 @@ __global__ __launch_bounds__(kTrNT, 2) void k_trsv(TrsvArgs g)
             __syncthreads();
             Acc<P> a0 = acc_zero<P>(), a1 = acc_zero<P>();
 #pragma unroll 1
-            for (int k = 4 * wid, nt = 0; k < B; ++k) {  // U_j^-1 is upper triangular
-                const V<P> u = at(lds.inv, k, row);
-                acc_fma(a0, u, at(lds.nxt, c0, k));
-                acc_fma(a1, u, at(lds.nxt, c0 + 16, k));
+            for (int k = 4 * wid, nt = 0; k < B; ++k) {
+                if (k >= row) {  // U_j^-1 is upper triangular; a product with its zeros would spread a NaN or Inf of row k downwards
+                    const V<P> u = at(lds.inv, k, row);
+                    acc_fma(a0, u, at(lds.nxt, c0, k));
+                    acc_fma(a1, u, at(lds.nxt, c0 + 16, k));
+                }
                 if (++nt % kLazy<P> == 0) {
                     a0 = acc_from(acc_get(a0));
                     a1 = acc_from(acc_get(a1));
@@ -2307,8 +2309,8 @@ __global__ __launch_bounds__(kTrNT, 2) void k_trsv(TrsvArgs g)
         V<P> xj;
         {
             Acc<P> t0 = acc_zero<P>(), t1 = acc_zero<P>();
-            acc_fma(t0, at(lds.inv, c0, row), lds_ld<P>(&lds.v[c0 * P]));
-            acc_fma(t1, at(lds.inv, c0 + 16, row), lds_ld<P>(&lds.v[(c0 + 16) * P]));
+            if (c0 >= row) acc_fma(t0, at(lds.inv, c0, row), lds_ld<P>(&lds.v[c0 * P]));
+            if (c0 + 16 >= row) acc_fma(t1, at(lds.inv, c0 + 16, row), lds_ld<P>(&lds.v[(c0 + 16) * P]));
             acc_add_acc(t0, t1);
             xj = row_sum(t0);
         }

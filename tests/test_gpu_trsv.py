@@ -102,3 +102,29 @@ def test_trsv_status_of_a_wait_that_gave_up(P, n):
             assert int(info.item()) == -1 or torch.equal(x, ref), rep
     finally:
         M.set_tuning(mdls.MDLS_TUNE_SPIN_LIMIT, saved)
+
+
+@pytest.mark.parametrize("bad", (np.nan, np.inf))
+@pytest.mark.parametrize("P,n", [(1, 90), (2, 90), (4, 90), (8, 70), (1, 800), (2, 800), (4, 800), (8, 1184)])
+def test_trsv_nan_and_inf_stay_above(P, n, bad):
+    """A NaN or Inf in y(r), in R(r, r) or in R(r, c) reaches x(0:r+1) and leaves every x below row r as it
+    is, bit for bit, wherever r lies in a block of rows."""
+    import paper_2110_08375_amd as M
+
+    print("case trsv nan P=%d n=%d %s" % (P, n, bad), flush=True)
+    U, _, y = problem(P, n, n)
+    Ug, yg = torch.from_numpy(U).cuda(), torch.from_numpy(y).cuda()
+    ref, _ = M.backsub(P, Ug, yg.clone(), 1)
+    assert bool(torch.isfinite(ref).all())
+    for r in (0, 5, 18, 31, 32, 50, n - 2):
+        yb = yg.clone()
+        yb[0, r] = bad
+        x, _ = M.backsub(P, Ug, yb, 1)
+        assert torch.equal(x[:, r + 1:], ref[:, r + 1:]), ("y", r)
+        assert not bool(torch.isfinite(x[0, r])), ("y", r)
+        for c in (r, r + 1, min(n - 1, r + 32), n - 1):
+            Ub = Ug.clone()
+            Ub[0, c, r] = bad
+            x, _ = M.backsub(P, Ub, yg.clone(), 1)
+            assert torch.equal(x[:, r + 1:], ref[:, r + 1:]), ("R", r, c)
+            assert np.isinf(bad) and r == c or not bool(torch.isfinite(x[0, r])), ("R", r, c)
