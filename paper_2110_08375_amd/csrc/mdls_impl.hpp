@@ -2373,6 +2373,32 @@ __global__ __launch_bounds__(kThreads) void k_trsv_init(unsigned long long *xw, 
 }  // namespace
 
 // ============================================================================ T, W, Q^T B helpers
+// G(l, j) = y_l^T y_j (l < j) for tile block k: block (j, k), one wave per l.  The form for od and for tiles of
+// fewer than 96 columns, whose 16 x 16 blocks of sums (k_gemm) leave the chip idle (gram_blocks).
+template <int P>
+__global__ __launch_bounds__(kThreads) void k_gram(const double *A, long lda, long ps, int m, int tile, double *G,
+                                                  long gps)
+{
+    const int j = blockIdx.x, k = blockIdx.y;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const long kt = (long)k * tile;
+    const double *Y = A + kt * lda + kt;
+    const int h = m - (int)kt;
+    double *Gk = G + kt * tile;
+    for (int l = wid; l < tile; l += 4) {
+        if (l >= j) {
+            if (lane == 0) stm(Gk, gps, (long)j * tile + l, zero<P>());
+            continue;
+        }
+        Acc<P> acc = acc_zero<P>();
+        int nt = 0;
+        for (int r = j + lane; r < h; r += 64)  // y_j is zero above row j
+            acc_fma_step(acc, y_entry<P>(Y, lda, ps, r, l, h, tile), y_entry<P>(Y, lda, ps, r, j, h, tile), nt++);
+        const V<P> s = wave_sum(acc_get(acc));
+        if (lane == 0) stm(Gk, gps, (long)j * tile + l, s);
+    }
+}
+
 // W(r, k*tile + j) = -sum_{l<=j} Y_k(r, l) T_k(l, j) for r >= k*tile; zero above.
 template <int P>
 __global__ __launch_bounds__(kThreads) void k_form_w(const double *A, long lda, long ps, const double *T, long ldt,
@@ -2412,7 +2438,41 @@ __global__ __launch_bounds__(kThreads) void k_tn(const double *Y, long lda, long
     if (lane == 0) stm(S, sps, (long)c * tile + l, s);
 }
 
-// The products of a few columns (fewer than kGemmCols): U(i, c) = sum_l op(T)(i, l) S(l, c), one
+// U(i, c) = sum_l op(T)(i, l) S(l, c) (op(T) = T^T: l <= i, or T: l >= i), one thread per (i, c): for tiles of at
+// most four columns, whose sums are too short for a wave (od, tile 1 and 4: 7 and 14 us a launch, k_trmm_v 13 and 18).
+template <int P, bool TRANS>
+__global__ __launch_bounds__(kThreads) void k_trmm(const double *T, long ldt, long tps, const double *S, long sps,
+                                                  double *U, int tile, int nrhs, const int *skip)
+{
+    if (skip && *skip) return;
+    const int i = blockIdx.x * kThreads + threadIdx.x, c = blockIdx.y;
+    if (i >= tile || c >= nrhs) return;
+    Acc<P> acc = acc_zero<P>();
+    int nt = 0;
+    for (int l = TRANS ? 0 : i; l < (TRANS ? i + 1 : tile); ++l)
+        acc_fma_step(acc, ldm<P>(T, tps, TRANS ? (long)i * ldt + l : (long)l * ldt + i),
+                     ldm<P>(S, sps, (long)c * tile + l), nt++);
+    stm(U, sps, (long)c * tile + i, acc_get(acc));
+}
+
+// B(r, c) -= sum_l Y(r, l) U(l, c), one thread per row: for one or two columns of Y, and for a few of them where
+// the rows alone fill the chip (qd, tile 8, 2048 rows x 256 columns: 19 us a launch, k_nn_sub_v 28, k_gemm 26).
+template <int P>
+__global__ __launch_bounds__(kThreads) void k_nn_sub(const double *Y, long lda, long ps, int h, int tile, const double *U,
+                                                    long ups, double *B, long ldb, long bps, const int *skip)
+{
+    if (skip && *skip) return;
+    const long r = (long)blockIdx.x * kThreads + threadIdx.x;
+    const int c = blockIdx.y;
+    if (r >= h) return;
+    Acc<P> acc = acc_from(ldm<P>(B, bps, (long)c * ldb + r));
+    const long lmax = ((long)tile - 1 < r) ? (long)tile - 1 : r;
+    for (int l = 0; l <= (int)lmax; ++l)
+        acc_fma_step(acc, neg(y_entry<P>(Y, lda, ps, r, l, h, tile)), ldm<P>(U, ups, (long)c * tile + l), l);
+    stm(B, bps, (long)c * ldb + r, acc_get(acc));
+}
+
+// The products where k_gemm's blocks are too few: U(i, c) = sum_l op(T)(i, l) S(l, c), one
 // wave per (i, c), the lanes over l (op(T) = T^T: l <= i, or T: l >= i).  One thread per output with
 // its chain of tile multiply-adds took 13.6 us for one dd column and tile 128; this takes 3.2.
 template <int P, bool TRANS>
@@ -2494,7 +2554,6 @@ __global__ __launch_bounds__(kThreads) void k_nn_sub_v(const double *Y, long lda
 // 77 % of that rate for the first two (one wave per (l, c), one thread per row and one thread per (i, c)
 // before, 64 columns at a time: 4.66, 9.77 and 10.2 ms).
 enum { kTN, kTT, kTNo, kNN, kGram };
-constexpr int kGemmCols = 16;  // fewer columns take the wave-per-output kernels
 
 struct GemmArgs {
     const double *X;  // Y (unit lower trapezoidal, h x tile) or T
@@ -3266,6 +3325,12 @@ int solve_t(int m, int n, int tile, double *A, int lda, double *b, double *x, vo
     return hipGetLastError() == hipSuccess ? 0 : MDLS_EHIP;
 }
 
+// Whether the tiles' Gram blocks are formed in blocks of sums (k_gemm) or a wave each (k_gram).  2048 rows, k_gram
+// against k_gemm, one to eight tiles: dd 117-127 / 365 us at tile 32, 220-239 / 362 at 64, 386-469 / 363 at 128,
+// 806-1138 / 370-425 at 256; qd 183-196 / 645, 345-418 / 650, 681-1156 / 653-898, 1256-3296 / 675-2429; od
+// 633 / 4070, 1270-2101 / 4080, 2433-4103 / 4100-4425, 4639-7748 / 4272-7462.
+constexpr bool gram_blocks(int P, int tile) { return P <= 4 && tile >= 96; }
+
 template <int P>
 int qr_impl(int m, int n, int tile, double *A, int lda, double *beta, double *T, int ldt, void *ws, int *d_info,
             hipStream_t s, double *split)
@@ -3282,11 +3347,16 @@ int qr_impl(int m, int n, int tile, double *A, int lda, double *beta, double *T,
         const int N = n / tile;
         double *G = cx.big();
         const long gps = (long)tile * n;
-        constexpr int BT = 16 * gemm_rb<P>();
-        const int nb = (tile + BT - 1) / BT;
-        const GemmArgs ga{A, (long)lda, psa, nullptr, 0, 0, G, (long)tile, gps, m, tile, tile, (long)tile * (lda + 1),
-                          (long)tile * tile, nullptr};
-        MDLS_LAUNCH("k_gram", P, 0, (k_gemm<P, kGram>), dim3(nb, nb, N), dim3(kThreads), s, ga);
+        if constexpr (gram_blocks(P, 256)) {
+            constexpr int BT = 16 * gemm_rb<P>();
+            const int nb = (tile + BT - 1) / BT;
+            const GemmArgs ga{A, (long)lda, psa, nullptr, 0, 0, G, (long)tile, gps, m, tile, tile, (long)tile * (lda + 1),
+                              (long)tile * tile, nullptr};
+            if (gram_blocks(P, tile))
+                MDLS_LAUNCH("k_gram", P, 0, (k_gemm<P, kGram>), dim3(nb, nb, N), dim3(kThreads), s, ga);
+        }
+        if (!gram_blocks(P, tile))
+            MDLS_LAUNCH("k_gram", P, 0, (k_gram<P>), dim3(tile, N), dim3(kThreads), s, A, (long)lda, psa, m, tile, G, gps);
         InvArgs ia;
         ia.U = G;
         ia.ldu = tile;
@@ -3319,32 +3389,94 @@ int qr_split_t(int m, int n, int tile, double *A, int lda, double *T, int ldt, v
     return qr_impl<P>(m, n, tile, A, lda, nullptr, T, ldt, ws, nullptr, s, split);
 }
 
+// The form of each of a tile block's three products.  A thread of k_gemm forms its outputs' whole sums, so a
+// launch lasts as long as one sum while its blocks are fewer than the chip takes at once, and its waste is
+// the part of the blocks that hold no output; a wave (k_tn, k_trmm_v, k_nn_sub_v) forms one output, or 64 rows of
+// them, with the sum split, at more instructions per multiply-add (dd and double: up to three times, qd 1.2, od
+// 1.05).  So k_gemm takes over from a number of full blocks on, whatever the length of the sums, where enough of
+// them is output.  Measured for 16 to 2048 columns, tiles of 8 to 256 and 256 to 2048 rows, time of the wave
+// form over k_gemm's with the blocks of the launch: Y^T B dd 0.5 at 32, 0.8 at 64, 1.4 at 128, 2.6 at 256;
+// qd 0.7-1.1 at 128, 1.2 at 256; od 0.5-0.7 at 128, 1.0-1.2 at 256.  B -= Y U dd 0.8-1.0 at 128, 1.1-1.4 at
+// 256; qd 0.8-1.1 at 256, 1.0-1.3 at 512; od 0.9-1.05 up to 4096: never k_gemm.  op(T) S, tile 32, 64, 128,
+// 256: qd 1 at 16, 32, 64, 120 blocks; od 34, 64, 125, 200; dd 20, 30, 55, 90.  (k_gemm for every call of 16
+// columns or more, as it was: dd 1000 x 32, tile 32, 16 columns 187 us in place of 33, od 2150 in place of 225.)
+enum { kRowForm, kWaveForm, kBlockForm };
+
+template <int P>
+int gemm_or(double need, int rows, int nc, int else_form)
+{
+    constexpr int BT = 16 * gemm_rb<P>();
+    constexpr double useful = P <= 2 ? 0.5 : (P == 4 ? 0.8 : 0.9);
+    const double out = (double)rows * nc;
+    const double full = out / (BT * BT), launched = (double)((rows + BT - 1) / BT) * ((nc + BT - 1) / BT);
+    return full >= need && full >= useful * launched ? kBlockForm : else_form;
+}
+
+template <int P>
+int tn_form(int tile, int nc)
+{
+    return gemm_or<P>(P <= 2 ? 96 : (P == 4 ? 192 : 256), tile, nc, kWaveForm);
+}
+
+template <int P>
+int trmm_form(int tile, int nc)
+{
+    if (tile <= 4) return kRowForm;
+    return gemm_or<P>(P <= 2 ? 16 + tile / 4 : (P == 4 ? std::max(12, tile / 2) : std::max(24, tile)), tile, nc, kWaveForm);
+}
+
+template <int P>
+int nn_form(int h, int tile, int nc)
+{
+    constexpr int BT = 16 * gemm_rb<P>();
+    if (tile <= 2 || (tile <= (P < 8 ? 8 : 16) && (double)h * nc >= 192.0 * BT * BT)) return kRowForm;
+    return P < 8 ? gemm_or<P>(P <= 2 ? 160 : 256, h, nc, kWaveForm) : kWaveForm;
+}
+
 // One tile block on nc columns of B: S = Y^T B, U = op(T) S, B -= Y U (op(T) = T^T for Q^T, T for Q);
-// h rows from the block's diagonal.  kGemmCols columns or more go in 16 x 16 blocks of outputs (qd, tile
-// 128, n = 1024: 39 us a tile block and 64 columns for the three kernels, 192 with a wave or a thread per
-// output); fewer, where those blocks would be mostly empty, one wave per output.
+// h rows from the block's diagonal.
 template <int P, bool TRANS>
 void apply_block(const double *Y, long lda, long psa, int h, int tile, const double *Tk, long ldt, long tps, double *B,
                  long ldb, long bps, int nc, double *S, double *U, long sps, const int *skip, hipStream_t s)
 {
     const double tri = 0.5 * tile * tile * nc, full = (double)h * tile * nc;
-    if (nc < kGemmCols) {
-        MDLS_LAUNCH("k_tn", P, full, (k_tn<P>), dim3((tile + 3) / 4, nc), dim3(kThreads), s, Y, lda, psa, h, tile, B, ldb,
-                    bps, nc, S, sps, skip);
-        MDLS_LAUNCH("k_trmm", P, tri, (k_trmm_v<P, TRANS>), dim3((tile + 3) / 4, nc), dim3(kThreads), s, Tk, ldt, tps, S,
-                    sps, U, tile, nc, skip);
-        MDLS_LAUNCH("k_nn_sub", P, full, (k_nn_sub_v<P>), dim3((h + 63) / 64, nc), dim3(kThreads), s, Y, lda, psa, h, tile,
-                    U, sps, B, ldb, bps, skip);
-        return;
-    }
     constexpr int BT = 16 * gemm_rb<P>();
     const unsigned bt = (tile + BT - 1) / BT, bh = (h + BT - 1) / BT, bc = (nc + BT - 1) / BT;
-    const GemmArgs a1{Y, lda, psa, B, ldb, bps, S, (long)tile, sps, h, tile, nc, 0, 0, skip};
-    const GemmArgs a2{Tk, ldt, tps, S, (long)tile, sps, U, (long)tile, sps, h, tile, nc, 0, 0, skip};
-    const GemmArgs a3{Y, lda, psa, U, (long)tile, sps, B, ldb, bps, h, tile, nc, 0, 0, skip};
-    MDLS_LAUNCH("k_tn", P, full, (k_gemm<P, kTN>), dim3(bt, bc), dim3(kThreads), s, a1);
-    MDLS_LAUNCH("k_trmm", P, tri, (k_gemm<P, TRANS ? kTT : kTNo>), dim3(bt, bc), dim3(kThreads), s, a2);
-    MDLS_LAUNCH("k_nn_sub", P, full, (k_gemm<P, kNN>), dim3(bh, bc), dim3(kThreads), s, a3);
+    if (tn_form<P>(tile, nc) == kBlockForm) {
+        const GemmArgs ga{Y, lda, psa, B, ldb, bps, S, (long)tile, sps, h, tile, nc, 0, 0, skip};
+        MDLS_LAUNCH("k_tn", P, full, (k_gemm<P, kTN>), dim3(bt, bc), dim3(kThreads), s, ga);
+    } else {
+        MDLS_LAUNCH("k_tn", P, full, (k_tn<P>), dim3((tile + 3) / 4, nc), dim3(kThreads), s, Y, lda, psa, h, tile, B, ldb,
+                    bps, nc, S, sps, skip);
+    }
+    switch (trmm_form<P>(tile, nc)) {
+    case kBlockForm: {
+        const GemmArgs ga{Tk, ldt, tps, S, (long)tile, sps, U, (long)tile, sps, h, tile, nc, 0, 0, skip};
+        MDLS_LAUNCH("k_trmm", P, tri, (k_gemm<P, TRANS ? kTT : kTNo>), dim3(bt, bc), dim3(kThreads), s, ga);
+        break;
+    }
+    case kRowForm:
+        MDLS_LAUNCH("k_trmm", P, tri, (k_trmm<P, TRANS>), dim3((tile + kThreads - 1) / kThreads, nc), dim3(kThreads), s, Tk,
+                    ldt, tps, S, sps, U, tile, nc, skip);
+        break;
+    default:
+        MDLS_LAUNCH("k_trmm", P, tri, (k_trmm_v<P, TRANS>), dim3((tile + 3) / 4, nc), dim3(kThreads), s, Tk, ldt, tps, S,
+                    sps, U, tile, nc, skip);
+    }
+    const int nf = nn_form<P>(h, tile, nc);
+    if constexpr (P < 8) {
+        if (nf == kBlockForm) {
+            const GemmArgs ga{Y, lda, psa, U, (long)tile, sps, B, ldb, bps, h, tile, nc, 0, 0, skip};
+            MDLS_LAUNCH("k_nn_sub", P, full, (k_gemm<P, kNN>), dim3(bh, bc), dim3(kThreads), s, ga);
+            return;
+        }
+    }
+    if (nf == kRowForm)
+        MDLS_LAUNCH("k_nn_sub", P, full, (k_nn_sub<P>), dim3((h + kThreads - 1) / kThreads, nc), dim3(kThreads), s, Y, lda,
+                    psa, h, tile, U, sps, B, ldb, bps, skip);
+    else
+        MDLS_LAUNCH("k_nn_sub", P, full, (k_nn_sub_v<P>), dim3((h + 63) / 64, nc), dim3(kThreads), s, Y, lda, psa, h, tile,
+                    U, sps, B, ldb, bps, skip);
 }
 
 // B := Q^T B (TRANS: the tile blocks in order, B := (I - Y_k T_k^T Y_k^T) B) or B := Q B (the blocks

@@ -56,3 +56,41 @@ def test_apply_block_of_columns(orc, P, m, n, tile, nrhs):
     for j in range(n):  # upper triangular, betas on the diagonal
         assert np.all(Tn[:, j, j % tile + 1:] == 0.0)
         assert np.array_equal(Tn[:, j, j % tile], bt[:, j])
+
+
+# P, m, n, tile, columns of B: on both sides of where each of the three products changes form (a wave per output
+# or 64 rows, a thread per row, blocks of outputs); more columns than one launch takes, the last launch with few
+ROUTES = [
+    (2, 300, 256, 256, 352), (2, 300, 256, 256, 400), (2, 290, 256, 128, 700), (2, 1100, 16, 16, 150), (2, 2000, 8, 8, 130),
+    (2, 100, 60, 2, 40), (2, 100, 60, 4, 40), (2, 40, 33, 33, 3000),
+    (4, 280, 256, 256, 180), (4, 280, 256, 256, 200), (4, 700, 48, 48, 100), (4, 1200, 32, 32, 64), (4, 600, 24, 8, 120),
+    (4, 90, 40, 1, 30), (4, 150, 96, 96, 205), (4, 64, 64, 64, 590),
+    (8, 260, 256, 256, 260), (8, 260, 256, 128, 130), (8, 200, 32, 16, 300), (8, 70, 20, 4, 20), (8, 60, 20, 1, 17),
+    (1, 300, 256, 256, 400), (1, 300, 64, 32, 700),
+]
+
+
+@pytest.mark.parametrize("P,m,n,tile,nrhs", ROUTES)
+def test_apply_form_of_the_products(P, m, n, tile, nrhs):
+    """All columns in one call against the same columns nine at a time (each a wave per output, held to the
+    oracle above): Q^T B and Q B agree to 64 m u whatever form the number of columns chooses, and Q Q^T B is B."""
+    import paper_2110_08375_amd as M
+
+    print("case apply form P=%d m=%d n=%d tile=%d nrhs=%d" % (P, m, n, tile, nrhs), flush=True)
+    Ag = torch.from_numpy(mdgen.md_uniform(P, m, n, 510 + m, mdgen.STREAM_A)).cuda()
+    B = mdgen.md_uniform(P, m, nrhs, 610 + m, mdgen.STREAM_B)
+    Bg = torch.from_numpy(B).cuda()
+    T = torch.full((P, n, tile), 7.0, dtype=torch.float64, device="cuda")
+    M.qr(P, Ag, tile, T=T)
+    tol = 64 * m * unit(P)
+    for apply in (M.apply_qt, M.apply_q):
+        few = Bg.clone()
+        for c in range(0, nrhs, 9):
+            part = few[:, c:c + 9].contiguous()
+            apply(P, Ag, T, part, tile)
+            few[:, c:c + 9] = part
+        apply(P, Ag, T, Bg, tile)
+        err = md_err(Bg.cpu().numpy(), few.cpu().numpy())
+        print("  %.2f u" % (err / unit(P)), flush=True)
+        assert err <= tol
+    assert md_err(Bg.cpu().numpy(), B) <= 2 * tol
