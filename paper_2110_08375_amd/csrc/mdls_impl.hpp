@@ -2520,8 +2520,8 @@ __global__ __launch_bounds__(kThreads) void k_nn_sub_v(const double *Y, long lda
 #pragma unroll
         for (int k = 0; k < NA; ++k) y[k] = (l + k < le) ? y_entry<P>(Y, lda, ps, r, l + k, h, tile) : zero<P>();
 #pragma unroll
-        for (int k = 0; k < NA; ++k)
-            if (l + k < le) acc_fma(acc[k], y[k], lds_ld<P>(&su[(l + k) * P]));
+        for (int k = 0; k < NA; ++k)  // not with Y's zeros: U(l) may be NaN or Inf, and row r < l does not depend on it
+            if (l + k < le && l + k <= r) acc_fma(acc[k], y[k], lds_ld<P>(&su[(l + k) * P]));
         if ((++nt) % kLazy<P> == 0) {
 #pragma unroll
             for (int a = 0; a < NA; ++a) acc[a] = acc_from(acc_get(acc[a]));
@@ -2549,7 +2549,10 @@ __global__ __launch_bounds__(kThreads) void k_nn_sub_v(const double *Y, long lda
 //   kTNo   U = T S            X(i, k) = T(i, k), k >= i
 //   kNN    B -= Y U           X(i, k) = Y(i, k)
 //   kGram  G = striu(Y^T Y)   as kTN with Z = Y; tile block blockIdx.z
-// A block skips the k where its X is zero.  Bound by the FP64 instruction rate: qd, m = n = 1024,
+// A block skips the k where its X is zero.  In the chunks that hold zeros for some of its rows (kTT and kNN,
+// k > i) the products with them are left out too: Z(k, c) may be NaN or Inf, on which row i does not depend.
+// (kTN, kTNo and kGram need no such care: there a NaN Z(k, c) makes all of the product that follows NaN.)
+//  Bound by the FP64 instruction rate: qd, m = n = 1024,
 // tile 128, all 1024 columns, 2.31 ms for the eight Y^T B, 2.17 for B -= Y U and 0.54 for T S, 72 to
 // 77 % of that rate for the first two (one wave per (l, c), one thread per row and one thread per (i, c)
 // before, 64 columns at a time: 4.66, 9.77 and 10.2 ms).
@@ -2654,27 +2657,35 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g)
         const int buf = nch & 1;
         const bool more = k0 + KC < ke;
         if (more) fetch(k0 + KC);
+        auto chunk = [&](auto edge) __attribute__((always_inline)) {
 #pragma unroll 1
-        for (int k = 0; k < KC; ++k) {
-            V<P> x[RB], z[RB];
+            for (int k = 0; k < KC; ++k) {
+                V<P> x[RB], z[RB];
 #pragma unroll
-            for (int a = 0; a < RB; ++a) {
-                x[a] = lds_ld<P>(&sX[buf][k * LD + (tx + 16 * a) * P]);
-                z[a] = lds_ld<P>(&sZ[buf][k * LD + (ty + 16 * a) * P]);
-            }
+                for (int a = 0; a < RB; ++a) {
+                    x[a] = lds_ld<P>(&sX[buf][k * LD + (tx + 16 * a) * P]);
+                    z[a] = lds_ld<P>(&sZ[buf][k * LD + (ty + 16 * a) * P]);
+                }
 #pragma unroll
-            for (int a = 0; a < RB; ++a)
+                for (int a = 0; a < RB; ++a)
+                    if (!decltype(edge)::value || k0 + k <= i0 + tx + 16 * a) {
 #pragma unroll
-                for (int b = 0; b < RB; ++b) acc_fma(acc[a][b], x[a], z[b]);
-            if constexpr (kLazy<P> < KC) {
-                if ((k + 1) % kLazy<P> == 0) {
+                        for (int b = 0; b < RB; ++b) acc_fma(acc[a][b], x[a], z[b]);
+                    }
+                if constexpr (kLazy<P> < KC) {
+                    if ((k + 1) % kLazy<P> == 0) {
 #pragma unroll
-                    for (int a = 0; a < RB; ++a)
+                        for (int a = 0; a < RB; ++a)
 #pragma unroll
-                        for (int b = 0; b < RB; ++b) acc[a][b] = acc_from(acc_get(acc[a][b]));
+                            for (int b = 0; b < RB; ++b) acc[a][b] = acc_from(acc_get(acc[a][b]));
+                    }
                 }
             }
-        }
+        };
+        if ((MODE == kTT || MODE == kNN) && k0 + KC > i0 + 1)
+            chunk(std::true_type{});
+        else
+            chunk(std::false_type{});
         ++nch;
         if (nch % 4 == 0 || !more) {
 #pragma unroll

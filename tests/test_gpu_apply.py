@@ -94,3 +94,28 @@ def test_apply_form_of_the_products(P, m, n, tile, nrhs):
         print("  %.2f u" % (err / unit(P)), flush=True)
         assert err <= tol
     assert md_err(Bg.cpu().numpy(), B) <= 2 * tol
+
+
+@pytest.mark.parametrize("P,m,n,tile,nrhs", [(2, 90, 64, 64, 3), (2, 300, 256, 256, 400), (4, 90, 64, 64, 3),
+                                             (4, 300, 256, 256, 210), (8, 70, 48, 48, 3), (8, 270, 256, 256, 260),
+                                             (4, 60, 8, 2, 20), (1, 300, 256, 256, 400)])
+def test_apply_nan_column_leaves_the_rows_above(P, m, n, tile, nrhs):
+    """A NaN in column j of A makes that reflector and those after it NaN: the first j rows of Q^T B do not
+    depend on them and keep their bits, whatever form the products take."""
+    import paper_2110_08375_amd as M
+
+    print("case apply nan P=%d m=%d n=%d tile=%d nrhs=%d" % (P, m, n, tile, nrhs), flush=True)
+    A = mdgen.md_uniform(P, m, n, 520 + m, mdgen.STREAM_A)
+    Bg = torch.from_numpy(mdgen.md_uniform(P, m, nrhs, 620 + m, mdgen.STREAM_B)).cuda()
+    T = torch.zeros((P, n, tile), dtype=torch.float64, device="cuda")
+    Ag = torch.from_numpy(A).cuda()
+    M.qr(P, Ag, tile, T=T)
+    ref = M.apply_qt(P, Ag, T, Bg.clone(), tile)
+    for j in (3, tile // 2 + 1, n - 2):
+        An = A.copy()
+        An[0, j, j + 1] = np.nan
+        Ag = torch.from_numpy(An).cuda()
+        M.qr(P, Ag, tile, T=T)
+        out = M.apply_qt(P, Ag, T, Bg.clone(), tile)
+        assert bool(torch.isnan(out[0, :, j:]).all()), j
+        assert torch.equal(out[:, :, :j], ref[:, :, :j]), j
