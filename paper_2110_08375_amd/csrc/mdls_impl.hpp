@@ -2514,19 +2514,26 @@ __global__ __launch_bounds__(kThreads) void k_nn_sub_v(const double *Y, long lda
     Acc<P> acc[NA];
 #pragma unroll
     for (int a = 0; a < NA; ++a) acc[a] = acc_zero<P>();
-    int nt = 0;
-    for (int l = lb; l < le; l += NA) {
-        V<P> y[NA];
+    auto sums = [&](auto edge) __attribute__((always_inline)) {
+        int nt = 0;
+        for (int l = lb; l < le; l += NA) {
+            V<P> y[NA];
 #pragma unroll
-        for (int k = 0; k < NA; ++k) y[k] = (l + k < le) ? y_entry<P>(Y, lda, ps, r, l + k, h, tile) : zero<P>();
+            for (int k = 0; k < NA; ++k) y[k] = (l + k < le) ? y_entry<P>(Y, lda, ps, r, l + k, h, tile) : zero<P>();
 #pragma unroll
-        for (int k = 0; k < NA; ++k)  // not with Y's zeros: U(l) may be NaN or Inf, and row r < l does not depend on it
-            if (l + k < le && l + k <= r) acc_fma(acc[k], y[k], lds_ld<P>(&su[(l + k) * P]));
-        if ((++nt) % kLazy<P> == 0) {
+            for (int k = 0; k < NA; ++k)
+                if (l + k < le && (!decltype(edge)::value || l + k <= r)) acc_fma(acc[k], y[k], lds_ld<P>(&su[(l + k) * P]));
+            if ((++nt) % kLazy<P> == 0) {
 #pragma unroll
-            for (int a = 0; a < NA; ++a) acc[a] = acc_from(acc_get(acc[a]));
+                for (int a = 0; a < NA; ++a) acc[a] = acc_from(acc_get(acc[a]));
+            }
         }
-    }
+    };
+    // beside the diagonal not with Y's zeros: U(l) may be NaN or Inf, and row r < l does not depend on it
+    if ((int)blockIdx.x * 64 < le)
+        sums(std::true_type{});
+    else
+        sums(std::false_type{});
     acc_add_acc(acc[0], acc[1]);
     lds_st(&sp[wid][lane * P], acc_get(acc[0]));
     __syncthreads();
