@@ -3339,7 +3339,16 @@ int solve_t(int m, int n, int tile, double *A, int lda, double *b, double *x, vo
     Ctx<P> cx{(char *)ws, layout(P, m, n, tile), s};
     const long psa = (long)lda * n;
     if (qr_panels<P>(cx, m, n, A, lda, psa, b, m, m, 1) != 0) return MDLS_EHIP;
-    backsub_solve<P>(cx, n, A, lda, psa, b, m, x, n, d_info, false);
+    // a workgroup of the back substitution reads its rows of y only and writes its rows of x, so y may be x;
+    // where x lies over other elements of b (x == b with m > n), y is taken out first
+    const double *y = b;
+    long yps = m;
+    if (x < b + (size_t)P * m && b < x + (size_t)P * n && !(x == b && (m == n || P == 1))) {
+        MDLS_LAUNCH("k_copy", P, 0, k_copy, dim3((n + 255) / 256), dim3(256), s, b, (long)m, cx.yw(), (long)n, n, P);
+        y = cx.yw();
+        yps = n;
+    }
+    backsub_solve<P>(cx, n, A, lda, psa, y, yps, x, n, d_info, false);
     return hipGetLastError() == hipSuccess ? 0 : MDLS_EHIP;
 }
 

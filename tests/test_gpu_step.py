@@ -72,3 +72,24 @@ def test_step_grid_cap_and_lookahead_keep_the_bits(P, m, n):
             M.set_tuning(opt, saved)
     for o in out[1:]:
         assert all(np.array_equal(p, q) for p, q in zip(out[0], o))
+
+
+@pytest.mark.parametrize("P,m,n,off", [(2, 300, 100, 0), (2, 300, 100, 100), (4, 200, 150, 0), (4, 64, 64, 0), (4, 90, 64, 7),
+                                       (8, 80, 70, 0), (1, 300, 100, 0), (1, 300, 100, 30)])
+def test_solution_over_the_right_hand_side(P, m, n, off):
+    """x in b's own memory, at its start or further on, with m > n and m == n: the same bits as in
+    memory of its own."""
+    import paper_2110_08375_amd as M
+
+    print("case x over b P=%d m=%d n=%d off=%d" % (P, m, n, off), flush=True)
+    A = torch.from_numpy(mdgen.md_uniform(P, m, n, 5, mdgen.STREAM_A)).cuda()
+    b = torch.from_numpy(mdgen.md_vector(P, m, 6, mdgen.STREAM_B)).cuda()
+    ref, info = M.solve(P, A.clone(), b.clone(), 1)
+    assert int(info.item()) == 0
+    buf = torch.zeros(P * (m + n), dtype=torch.float64, device="cuda")
+    for _ in range(3):
+        bb, x = buf[:P * m].view(P, m), buf[off:off + P * n].view(P, n)
+        bb.copy_(b)
+        _, info = M.solve(P, A.clone(), bb, 1, x=x)
+        assert int(info.item()) == 0
+        assert torch.equal(x, ref)
