@@ -197,7 +197,9 @@ int mdls_form_w(int p, int m, int n, int tile, const double *A, int lda, const d
  * the leading n x n block of R (ldr >= n, entries below the diagonal are not read), n a
  * multiple of tile.  x holds y on entry (P planes of n doubles) and the solution on exit.
  * One launch works in blocks of 32 rows, whatever the tile: each block's workgroup inverts its
- * diagonal block and takes b_j -= A_{j,i} x_i as the blocks below publish their x_i.  *d_info: 0;
+ * diagonal block and takes b_j -= A_{j,i} x_i as the blocks below publish their x_i.  Small qd and
+ * most od systems of tiles of up to 128, where that is slower, go tile by tile: the n/tile diagonal
+ * tiles inverted, then x_i := U_i^{-1} b_i and b_j -= A_{j,i} x_i alternating.  *d_info: 0;
  * k > 0 for the first exactly zero R(k,k); -1 if a wait gave up.
  */
 int mdls_backsub(int p, int n, int tile, const double *R, int ldr, double *x, void *ws,

@@ -18,9 +18,10 @@
 //   Back substitution (Section 2, Algorithm 1):
 //     k_trsv   -- one launch, a workgroup per block of rows: its diagonal block inverted, the x of
 //                 the blocks below taken as they are published, b_j -= A_{j,i} x_i, x_j := U_j^{-1} b_j;
-//     k_invert, k_inv_blocks, k_bs_xi, k_bs_upd -- the refined solve's, whose corrections use the
-//                 diagonal tiles' inverses again: the inverses, then per tile x_i := U_i^{-1} b_i and
-//                 b_j -= A_{j,i} x_i for every j < i at once.
+//     k_invert, k_inv_blocks, k_bs_xi, k_bs_upd -- the tiled form, for the sizes where it is the faster
+//                 one (backsub_by_tiles) and for the refined solve, whose corrections use the diagonal
+//                 tiles' inverses again: the inverses, then per tile x_i := U_i^{-1} b_i and b_j -= A_{j,i} x_i
+//                 for every j < i at once.
 //   Q^T B and Q B: k_gemm, k_trmm_v and k_nn_sub_v, in blocks of outputs.
 //
 // Multiple-double numbers are P limb planes (limb 0 most significant); see md.hpp for the
@@ -2070,7 +2071,7 @@ __global__ __launch_bounds__(kThreads) void k_bs_upd(const double *Rc, long ldr,
 // Bound by the chain of nblk steps; the reading of R goes on beside it (the next blocks in flight).  Before,
 // the tiles were inverted in full, b^3/6 multiply-adds each, and every tile took three launches.  n = 128 (tile 32),
 // 1024 (tile 128), 8192 (tile 128), before and now: dd 61, 145, 840 -> 31, 105, 477 us, qd 98, 313, 1693 -> 96, 285,
-// 1298 us; od n = 1024 and 4096 1222, 3724 -> 1259, 3159 us; qd n = 17920, tile 256, 4058 -> 3196 us (past 256 blocks
+// 1298 us; od n = 4096 3724 -> 3159 us (below, by tiles: backsub_by_tiles); qd n = 17920, tile 256, 4058 -> 3196 us (past 256 blocks
 // the later workgroups start when the first end, and read R at 1.6 TB/s).
 // AH = 0: the last block's product, its sum, U_j^-1 and another sum all stand between x_{j+1} and x_j.
 // AH = 2: with M_a = U_j^-1 R_{j,j+a}, x_j = z_j - M_2 x_{j+2} - M_1 x_{j+1}, where z_j = U_j^-1 (y_j -
@@ -2196,7 +2197,7 @@ __global__ __launch_bounds__(kTrNT, 2) void k_trsv(TrsvArgs g)
             res[q] = zero<P>();
         }
         __syncthreads();
-        for (int i = B - 1; i >= 0; --i) {
+        for (int i = nr - 1; i >= 0; --i) {  // (the last block may have fewer rows than B)
             if (gq == (i & 15)) {
                 const V<P> xv = mul(acc_get(i >= 16 ? a[1] : a[0]), lds_ld<P>(&lds.diag[i * P]));
                 lds_st(&lds.row[i & 1][c * P], xv);
@@ -2207,7 +2208,7 @@ __global__ __launch_bounds__(kTrNT, 2) void k_trsv(TrsvArgs g)
             }
             __syncthreads();
             const V<P> xv = neg(lds_ld<P>(&lds.row[i & 1][c * P]));
-            const bool renorm = ((B - i) % kLazy<P>) == 0;
+            const bool renorm = ((nr - i) % kLazy<P>) == 0;
 #pragma unroll
             for (int q = 0; q < 2; ++q)
                 if (gq + 16 * q < i) {
@@ -3304,21 +3305,51 @@ void backsub_sweep(const Ctx<P> &cx, int n, int tile, const double *R, long ldr,
     }
 }
 
-// More row blocks than this and k_trsv works ahead of the chain (AH = 2).  n = 1024 (32 blocks) with AH = 2
-// and with AH = 0: dd 105 and 121 us, qd 285 and 322, od 1259 and 1400; n = 300 (10 blocks): dd 70 and 50,
-// qd 187 and 142, od 821 and 562.
+// More row blocks than this and k_trsv works ahead of the chain (AH = 2).  AH = 2 against AH = 0, us: double n = 704
+// (22 blocks) 54 / 54, 1024 65 / 72; dd 640 89 / 85, 704 92 / 91, 768 95 / 96, 1024 107 / 124; qd 640 234 / 227, 704
+// 243 / 242, 768 252 / 259, 1024 287 / 324; od 768 1089 / 980, 1024 1216 / 1147, 1280 (40 blocks) 1361 / 1358, 1408
+// 1432 / 1471.
 template <int P>
 constexpr int trsv_ahead()
 {
-    return 22;
+    return P <= 4 ? 22 : 40;
 }
 
-// Back substitution R x = y (y: P planes yps apart, may be x) in two launches; the words of x lie in the
+// Whether the back substitution runs by the caller's tiles (k_invert, k_inv_blocks, k_bs_*) and not in one launch.
+// k_trsv inverts its block on one compute unit, 32 steps of up to four od multiply-adds a lane (qd 70, od 290 us
+// alone), which the tile kernels spread over several and, for tiles below 32, shorten; they take 30 us a tile in
+// return.  One launch / tiles, us: qd n = 8, 16, 24, 32 in one tile 33 / 31, 45 / 39, 56 / 49, 71 / 58, 64 with
+// tile 32 79 / 76, tile 16 79 / 81; od one tile of 1, 8, 32 45 / 33, 84 / 70, 290 / 185; tile 8 n = 64 317 / 276,
+// 128 373 / 501; tile 16 n = 128 372 / 329, 256 480 / 552; tile 32 n = 256 482 / 414, 1024 1147 / 1157, 1280 1358 /
+// 1452; tile 48 n = 1152 1253 / 1075, 1440 1447 / 1274; tile 50 n = 500 680 / 804; tile 64 n = 192 425 / 425, 256 479 /
+// 456, 1024 1147 / 871, 4096 3167 / 3050, 5120 3625 / 4019; tile 96 n = 960 1088 / 937, 3072 2387 / 2295; tile 128 n = 896
+// 1031 / 1121, 1024 1147 / 1170 (1231 on the card that gave 1170), 2048 1872 / 1736, 2560 2089 / 2055, 3584 2702 / 2959.
+template <int P>
+constexpr bool backsub_by_tiles(int n, int tile)
+{
+    if (P < 4) return false;
+    if (P == 4) return tile <= 32 && n <= 64 && (n == tile || (tile >= 8 && n <= 4 * tile));
+    if (tile < 32) return n == tile || (tile >= 4 && n <= 8 * tile);
+    if (tile <= 48) return n <= 26 * tile;
+    return (tile == 64 || tile == 96 || tile == 128) && n >= tile * tile / 16 && n <= 262144 / tile;
+}
+
+// Back substitution R x = y (y: P planes yps apart, may be x).  In one launch: the words of x lie in the
 // trailing update's partial sums.  *d_info: the first exactly zero R(k,k), -1 for a time-out.
 template <int P>
-void backsub_solve(const Ctx<P> &cx, int n, const double *R, long ldr, long psr, const double *y, long yps, double *x,
-                   long xps, int *d_info, bool clear_err)
+void backsub_solve(const Ctx<P> &cx, int n, int tile, const double *R, long ldr, long psr, const double *y, long yps,
+                   double *x, long xps, int *d_info, bool clear_err)
 {
+    if constexpr (P >= 4) {
+        if (backsub_by_tiles<P>(n, tile)) {
+            if (y != cx.yw())
+                MDLS_LAUNCH("k_copy", P, 0, k_copy, dim3((n + 255) / 256), dim3(256), cx.s, y, yps, cx.yw(), (long)n, n, P);
+            backsub_prep<P>(cx, n, tile, R, ldr, psr, cx.big(), d_info);
+            backsub_sweep<P>(cx, n, tile, R, ldr, psr, cx.big(), cx.yw(), x, xps, nullptr);
+            if (!clear_err) MDLS_LAUNCH("k_fold_err", P, 0, k_fold_err, dim3(1), dim3(64), cx.s, cx.err(), d_info);
+            return;
+        }
+    }
     unsigned long long *xw = (unsigned long long *)cx.apart();
     const long nw = (long)P * n;
     const int nblk = (n + kTrB - 1) / kTrB;
@@ -3348,7 +3379,7 @@ int solve_t(int m, int n, int tile, double *A, int lda, double *b, double *x, vo
         y = cx.yw();
         yps = n;
     }
-    backsub_solve<P>(cx, n, A, lda, psa, y, yps, x, n, d_info, false);
+    backsub_solve<P>(cx, n, tile, A, lda, psa, y, yps, x, n, d_info, false);
     return hipGetLastError() == hipSuccess ? 0 : MDLS_EHIP;
 }
 
@@ -3586,7 +3617,7 @@ template <int P>
 int backsub_t(int n, int tile, const double *R, int ldr, double *x, void *ws, int *d_info, hipStream_t s)
 {
     Ctx<P> cx{(char *)ws, layout(P, n, n, tile), s};
-    backsub_solve<P>(cx, n, R, ldr, (long)ldr * n, x, n, x, n, d_info, true);
+    backsub_solve<P>(cx, n, tile, R, ldr, (long)ldr * n, x, n, x, n, d_info, true);
     return hipGetLastError() == hipSuccess ? 0 : MDLS_EHIP;
 }
 

@@ -128,3 +128,52 @@ def test_trsv_nan_and_inf_stay_above(P, n, bad):
             x, _ = M.backsub(P, Ub, yg.clone(), 1)
             assert torch.equal(x[:, r + 1:], ref[:, r + 1:]), ("R", r, c)
             assert np.isinf(bad) and r == c or not bool(torch.isfinite(x[0, r])), ("R", r, c)
+
+
+# on both sides of where the caller's tiles take over from the one launch, and where that works ahead of the chain
+TILES = [
+    (4, 8, 8), (4, 24, 8), (4, 32, 8), (4, 48, 24), (4, 64, 32), (4, 96, 32), (4, 64, 64), (4, 1, 1), (4, 2, 1),
+    (8, 1, 1), (8, 4, 2), (8, 32, 4), (8, 64, 8), (8, 72, 8), (8, 120, 20), (8, 31, 31), (8, 96, 32), (8, 96, 48), (8, 100, 50),
+    (8, 192, 64), (8, 256, 64), (8, 832, 32), (8, 864, 32), (8, 896, 128), (8, 1024, 128), (8, 576, 96), (8, 1280, 4),
+    (8, 1284, 4),
+]
+
+
+@pytest.mark.parametrize("P,n,tile", TILES)
+def test_backsub_form_by_tile(orc, P, n, tile):
+    import paper_2110_08375_amd as M
+
+    print("case backsub form P=%d n=%d tile=%d" % (P, n, tile), flush=True)
+    U, R, y = problem(P, n, n)
+    x, info = M.backsub(P, torch.from_numpy(R).cuda(), torch.from_numpy(y).cuda(), tile)
+    assert int(info.item()) == 0
+    ref, _ = orc.backsub(U, y)
+    k = float(np.linalg.cond(U[0].T))
+    err = md_err(x.cpu().numpy(), ref)
+    print("  %.2f u kappa" % (err / (unit(P) * k)), flush=True)
+    assert err <= 64 * n * unit(P) * max(1.0, k)
+
+
+@pytest.mark.parametrize("P,n,tile", [(8, 128, 16), (8, 1024, 128), (4, 32, 32)])
+def test_solve_by_tiles_reports(P, n, tile):
+    """Where the solve's back substitution goes by tiles: a zero column and a time-out of the factorisation
+    are reported as before."""
+    import paper_2110_08375_amd as M
+    from paper_2110_08375_amd import mdls
+
+    print("case solve by tiles P=%d n=%d" % (P, n), flush=True)
+    A = torch.from_numpy(mdgen.md_uniform(P, n, n, 9, mdgen.STREAM_A)).cuda()
+    b = torch.from_numpy(mdgen.md_vector(P, n, 9, mdgen.STREAM_B)).cuda()
+    Az = A.clone()
+    Az[:, n // 2, :] = 0.0
+    _, info = M.solve(P, Az, b.clone(), tile)
+    assert int(info.item()) == n // 2 + 1
+    saved = M.get_tuning(mdls.MDLS_TUNE_SPIN_LIMIT)
+    M.set_tuning(mdls.MDLS_TUNE_SPIN_LIMIT, 0)
+    try:
+        _, info = M.solve(P, A.clone(), b.clone(), tile)
+        assert int(info.item()) == (-1 if n > 64 else 0)
+    finally:
+        M.set_tuning(mdls.MDLS_TUNE_SPIN_LIMIT, saved)
+    _, info = M.solve(P, A.clone(), b.clone(), tile)
+    assert int(info.item()) == 0
