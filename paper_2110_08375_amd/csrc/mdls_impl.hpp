@@ -2946,6 +2946,16 @@ constexpr int step_rows()
     return P <= 2 ? 4096 : (P == 4 ? 2048 : 0);
 }
 
+// The last panel's update has no panel beside it and only B's columns: with more rows than this it goes to
+// k_apply_s/t/u, whose units cut them up, in place of one or two waves a column.  Solves of one column, us, k_step /
+// the three: double 1024 rows 39 / 39, 2048 43 / 40, 3000 53 / 36; dd 500 44 / 42, 768 50 / 40, 2048 64 / 42,
+// 4096 98 / 46; qd 64 55 / 52, 256 65 / 54, 768 101 / 54, 2048 135 / 56.
+template <int P>
+constexpr int step_tail_rows()
+{
+    return P == 1 ? 1024 : (P == 2 ? 512 : 128);
+}
+
 constexpr long kStepLd = 1L << 24;  // the step kernel's byte offsets (16 columns of lda doubles) stay below 2^32
 
 template <int P>
@@ -3182,7 +3192,10 @@ int qr_panels(const Ctx<P> &cx, int m, int n, double *A, long lda, long psa, dou
                 sa.a = apply_args(l - 1);
                 sa.a.ncol = sa.a.nc + sa.a.nb;
             }
-            launch_step<P>(sa, tu.apply_grid_cap, cx.s);
+            if (l == nleaves && sa.a.h > step_tail_rows<P>())
+                launch_apply<P>(cx, sa.a, 0, cx.s);
+            else
+                launch_step<P>(sa, tu.apply_grid_cap, cx.s);
         }
         return 0;
     }

@@ -93,3 +93,10 @@ def test_solution_over_the_right_hand_side(P, m, n, off):
         _, info = M.solve(P, A.clone(), bb, 1, x=x)
         assert int(info.item()) == 0
         assert torch.equal(x, ref)
+
+
+@pytest.mark.parametrize("P,m,n", [(4, 128, 5), (4, 129, 5), (4, 137, 12), (2, 512, 9), (2, 513, 9), (2, 545, 35), (1, 1024, 7),
+                                   (1, 1025, 7), (2, 600, 1)])
+def test_step_tail_edges(orc, P, m, n):
+    """The last panel's update of the right-hand side alone, at the rows from which it is cut up."""
+    test_step_edges(orc, P, m, n)
