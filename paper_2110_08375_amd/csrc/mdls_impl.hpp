@@ -3691,7 +3691,10 @@ inline BatchCost batch_cost(int P, const BatchDesc &d)
 // and the list is played through on kCUs workgroups (the members of a team take consecutive slots,
 // and the team starts with its last member).  Of a falling sequence of deadlines, from every problem
 // alone to every problem on its largest team, the plan with the shortest predicted end is kept; the
-// first one is kept at once where single workgroups already balance (many problems).  A fixed cap on
+// first one where no other ends 2.5 % earlier (the prediction is no better than that: qd, 64 problems of 16 x 16,
+// predicted 2 % earlier in teams: 257 us in teams, 193 alone; dd, 64 of 128 x 128, predicted 3 %: 990 and 1061), and
+// at once where none can: single workgroups
+// balance, or no team ends before the longest problem alone.  A fixed cap on
 // the workgroups in teams, in place of this, left the problems past the first eight of a batch of
 // 160 on one workgroup each: qd, 160 problems of up to 512 x 512, 61.3 ms against 16.2 ms now; dd, 512
 // problems, 15.3 against 9.6 ms.
@@ -3707,7 +3710,7 @@ inline std::vector<int> batch_schedule(int P, std::vector<BatchDesc> &plan)
     std::vector<int> team(cnt), best_team, order(cnt), best_order;
     std::vector<double> t(cnt);
     std::vector<BatchCost> cost(cnt);
-    double hi = 0.0, lo = 0.0, area = 0.0, best = 0.0;
+    double hi = 0.0, lo = 0.0, area = 0.0, best = 0.0, alone = 0.0;
     for (size_t q = 0; q < cnt; ++q) {
         cost[q] = batch_cost(P, plan[q]);
         hi = std::max(hi, cost[q].one);
@@ -3716,6 +3719,7 @@ inline std::vector<int> batch_schedule(int P, std::vector<BatchDesc> &plan)
     }
     for (int k = 0; k < kDeadlines; ++k) {
         const double D = hi * std::pow(lo / hi, (double)k / (kDeadlines - 1));
+        double busy = 0.0;
         for (size_t q = 0; q < cnt; ++q) {
             const BatchCost &c = cost[q];
             team[q] = 1;
@@ -3726,7 +3730,10 @@ inline std::vector<int> batch_schedule(int P, std::vector<BatchDesc> &plan)
                 t[q] = c.chain + c.shared / team[q];
             }
             order[q] = (int)q;
+            busy += t[q] * team[q];
         }
+        // no plan ends before its workgroups' time is spent, and shorter deadlines only add to it
+        if (k > 0 && busy >= best * kCUs) break;
         std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return t[x] > t[y]; });
         // the workgroups' times at which they come free, earliest on top
         std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
@@ -3742,12 +3749,13 @@ inline std::vector<int> batch_schedule(int P, std::vector<BatchDesc> &plan)
             end = std::max(end, start + t[q]);
             if (k > 0 && end >= best) break;  // no better than the plan kept so far
         }
-        if (k == 0 || end < best) {
+        if (k == 0) alone = end;
+        if (k == 0 || (end < best && end < 0.975 * alone)) {
             best = end;
             best_team = team;
             best_order = order;
         }
-        if (k == 0 && end <= 1.05 * area / kCUs) break;
+        if (k == 0 && std::max(area / kCUs, lo) >= 0.975 * alone) break;
     }
     std::vector<BatchDesc> sorted;
     std::vector<int> slots;
