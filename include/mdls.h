@@ -26,8 +26,8 @@
  * MDLS_EUNSUPPORTED for valid arguments the library does not handle (too many rows for the
  * panel kernel, or a device with too few compute units for its workgroups).
  * Numerical status is written asynchronously to the device int *d_info where a call has
- * one: 0 = success, k > 0 = R(k,k) is exactly zero (1-based), x then unspecified; -1 = a
- * grid barrier of the factorisation gave up waiting (see below), the results are unspecified.
+ * one: 0 = success, k > 0 = R(k,k) is exactly zero (1-based), x then unspecified; -1 = a wait of
+ * one workgroup for another gave up (see below), the results are unspecified.
  * NaN and Inf in the input propagate to the output unchecked (d_info stays 0 unless R(k,k) is
  * exactly zero).  No call throws.
  *
@@ -77,8 +77,8 @@ int mdls_finalize(void);
  * read from the environment.  Only MDLS_TUNE_PANEL_VARIANT, MDLS_TUNE_SPLIT_UPDATE and
  * MDLS_TUNE_CPANEL change results (the panel's workgroup shape and so its reduction order; the
  * rounding of the update products; the complex reflector's formulas); the others change only
- * speed or, for the spin limit, how long a grid barrier (or the complex panel's wait for the
- * previous column) polls before it reports -1 through *d_info.
+ * speed or, for the spin limit, how long a wait of one workgroup for another polls before it
+ * reports -1 through *d_info.
  *   MDLS_TUNE_LOOKAHEAD        1 (default): concurrent trailing update on the side stream after
  *                              mdls_init; 0: off.  Double, dd and qd factorisations of up to 4096 /
  *                              4096 / 2048 rows hold it in the panel's own launch and use no side

@@ -63,9 +63,9 @@ struct PanelArgs {
     unsigned long long *gtag;  // tagged words of the per-column exchange (tag_words), no word of them tagged
                                // tag0 + 1 .. tag0 + wact on entry
     unsigned tag0;  // column index of the panel's first column
-    int *err;       // set to 1 if a barrier times out
+    int *err;       // set to 1 if a wait times out
     int G;          // workgroups in the launch
-    unsigned spin;  // polls before a barrier gives up
+    unsigned spin;  // polls before a wait gives up
 };
 
 // Entry (r, c) of a block of Householder vectors stored below the diagonal of A: zero above
@@ -130,8 +130,9 @@ __device__ __forceinline__ double tagged_value(unsigned long long hi, unsigned l
 }
 
 // One whole wave: loads the words of up to N items (item u of lane i at base + off[u] + w stride, u
-// taken where act[u]) until all of them carry the tag.  The polls are bounded, and once another
-// wait has given up every 256th poll gives up too; a time-out raises *err.
+// taken where act[u]) until all of them carry the tag.  The polls are bounded (no sleep between them: a poll
+// takes as long, 0.18 us, with the sleep of grid_sync), and once another wait has given up every 256th poll
+// gives up too; a time-out raises *err.
 template <int P, int N>
 __device__ __forceinline__ void poll_tagged(const unsigned long long *base, const long (&off)[N], const long (&stride)[N],
                                             const bool (&act)[N], unsigned tag, unsigned long long (&wd)[N][2 * P],
@@ -1059,8 +1060,9 @@ struct StepArgs {
 };
 
 // Plane k of a column block at a 32-bit byte offset: base and plane in scalar registers, so a lane's
-// addresses cost one register (64-bit addresses of every limb and column, kept across the loops, spilled,
-// and their reloads waited for the loads in flight: qd 200 us a launch in place of 75).
+// addresses cost one register (64-bit addresses of every limb and column, kept across the loops, spilled
+// more, and their reloads waited for the loads in flight: qd 200 us a launch in place of 75).  What is left:
+// k_step<qd> takes all 256 registers of two waves a SIMD and spills 55 of them (224 bytes a lane), dd 2.
 template <int P>
 __device__ __forceinline__ V<P> ldm32(const double *X, long ps, unsigned boff)
 {
@@ -1301,8 +1303,8 @@ struct BatchArgs {
     unsigned *counter;  // zero on entry
     unsigned *tctr;     // per problem: kTeamCtrs barrier counters, zero on entry
     double *xch;        // per problem: T (W^2 P) and panel_run's exchange words (2 kTeamMax (W^2 + 2W) P doubles)
-    int *err;           // set if a team barrier times out
-    unsigned spin;      // polls before a team barrier gives up
+    int *err;           // set if a wait inside a team times out
+    unsigned spin;      // polls before a wait inside a team gives up
     int *info;          // per problem
     long long *times;   // per problem: start, end; or null
 };
@@ -2078,6 +2080,8 @@ __global__ __launch_bounds__(kThreads) void k_bs_upd(const double *Rc, long ldr,
 // sum_{i > j+2} R_ji x_i) is ready before x_{j+2} comes: a step is one exchange, two multiply-adds a thread and
 // one sum in the wave.  The M_a are formed at the start, which costs the first steps their wait (qd 80 us),
 // so this form takes over where the chain is long (trsv_ahead).
+// Registers: dd 93 / 119 (AH = 0 / 2), qd 170 / 218; od takes all 256 of two waves a SIMD and spills 28 / 122 of them
+// (92 / 356 bytes a lane).
 constexpr int kTrB = 32;    // rows of a block
 constexpr int kTrNT = 512;  // threads of a workgroup
 constexpr unsigned long long kTrEmpty = 0x7ff4000000007153ull;
@@ -2555,8 +2559,8 @@ __global__ __launch_bounds__(kThreads) void k_nn_sub_v(const double *Y, long lda
 //   kTN    S = Y^T B          X(i, k) = Y(k, i)
 //   kTT    U = T^T S          X(i, k) = T(k, i), k <= i
 //   kTNo   U = T S            X(i, k) = T(i, k), k >= i
-//   kNN    B -= Y U           X(i, k) = Y(i, k)
-//   kGram  G = striu(Y^T Y)   as kTN with Z = Y; tile block blockIdx.z
+//   kNN    B -= Y U           X(i, k) = Y(i, k); not od
+//   kGram  G = striu(Y^T Y)   as kTN with Z = Y; tile block blockIdx.z; not od
 // A block skips the k where its X is zero.  In the chunks that hold zeros for some of its rows (kTT and kNN,
 // k > i) the products with them are left out too: Z(k, c) may be NaN or Inf, on which row i does not depend.
 // (kTN, kTNo and kGram need no such care: there a NaN Z(k, c) makes all of the product that follows NaN.)
@@ -2760,9 +2764,9 @@ struct Tuning {
     int panel_variant;     // 0: default panel shape, 1: the alternative shape (more rows per thread)
     int apply_grid_cap;    // > 0: workgroups of a concurrent trailing update; 0: the built-in rule
     int apply_wide_rows;   // od: trailing updates of at least this many rows take two workgroups per CU
-    unsigned spin_limit;   // polls before a grid barrier gives up
+    unsigned spin_limit;   // polls before a wait of one workgroup for another gives up
     int split_update;      // 1: the refined solve's factorisation forms Y^T C on the matrix cores
-    int cpanel;            // complex QR panels: 0 a launch per column, 1 persistent, 2 persistent for qd and od
+    int cpanel;            // complex QR panels: 0 a launch per column, 1 persistent, 2 the faster form of each (cqr_t)
 };
 Tuning tuning();
 int apply_grid_cap(int P, int h);
@@ -2940,6 +2944,9 @@ void launch_panel(const PanelArgs &a, PanelCfg cf, hipStream_t s)
 
 // The factorisation step kernel takes the default panel shape of P <= 4 up to this many rows.  A wave
 // of it updates whole columns, so beyond them the columns of a tall matrix, few and long, outlast the panel.
+// k_panel and k_apply_s/t/u on two streams over k_step, in time, for n = 64, 256 and (up to 4096 rows) 1024: double
+// 4096 rows 1.09, 1.14, 1.40, 6144 1.03, 1.11, 8192 0.96, 1.03; dd 3072 rows 1.07, 1.12, 1.27, 4096 0.97, 1.02, 1.29,
+// 6144 0.84, 0.89; qd 1536 rows 1.04, 1.08, 1.06, 2048 0.96, 1.01, 0.99, 3072 0.79, 0.86, 1.06.
 template <int P>
 constexpr int step_rows()
 {
@@ -2973,8 +2980,9 @@ void launch_step(const StepArgs &a, int grid_cap, hipStream_t s)
         if (u.ncol > 0) work += (2.0 * u.h * u.wact + 0.5 * u.wact * (u.wact + 1)) * u.ncol;
         // two waves share a column of more than 1024 (dd) or 768 (qd) rows: alone a wave takes 67 us (dd)
         // or 100 us (qd) for 1024 rows of it, and the panel beside it 77 or 88; below, one wave has
-        // half the staging (dd n = 1024: 4.86 ms against 4.93; qd n = 1024 with one wave throughout 12.5
-        // against 12.1)
+        // half the staging.  Time with one wave over that with two, n = 64, 128, 512, 1024: dd 1024 rows 1.02, 1.01,
+        // 1.00, 0.99, 1536 1.03, 1.02, 1.00, 1.00, 2048 1.08, 1.09, 1.04, 0.99; qd 768 rows 1.03, 1.01, 0.99 (n = 512), 1024
+        // 1.11, 1.09, 1.01, 1.00, 2048 1.52, 1.55, 1.43, 1.14; double 0.99 to 1.01 throughout
         StepArgs b = a;
         b.a.rs = u.h > (P <= 2 ? 1024 : 768) ? 2 : 1;
         const int ncw = NW / b.a.rs;
@@ -3470,7 +3478,7 @@ int qr_split_t(int m, int n, int tile, double *A, int lda, double *T, int ldt, v
 // qd 0.7-1.1 at 128, 1.2 at 256; od 0.5-0.7 at 128, 1.0-1.2 at 256.  B -= Y U dd 0.8-1.0 at 128, 1.1-1.4 at
 // 256; qd 0.8-1.1 at 256, 1.0-1.3 at 512; od 0.9-1.05 up to 4096: never k_gemm.  op(T) S, tile 32, 64, 128,
 // 256: qd 1 at 16, 32, 64, 120 blocks; od 34, 64, 125, 200; dd 20, 30, 55, 90.  (k_gemm for every call of 16
-// columns or more, as it was: dd 1000 x 32, tile 32, 16 columns 187 us in place of 33, od 2150 in place of 225.)
+// columns or more: dd 1000 x 32, tile 32, 16 columns 187 us and not 24, od 2150 and not 102.)
 enum { kRowForm, kWaveForm, kBlockForm };
 
 template <int P>
@@ -3672,8 +3680,13 @@ inline BatchLayout batch_layout(int P, int count)
 
 // Predicted milliseconds of one m x n problem on a team of T workgroups (one per CU): a column's
 // serial chain (longer where a team meets) plus the multiply-adds shared by the team.  The constants
-// are fitted to single problems and to 256 and 512 equal ones of 64 x 64 to 512 x 512, T = 1 and 16,
-// on MI355X (dd 512 x 512: 28.7 ms on one workgroup, 5.0 on 16; qd 128 and 14.9), and hold within 15 %.
+// were fitted to single problems and to 256 and 512 equal ones of 64 x 64 to 512 x 512, T = 1 and 16, on MI355X
+// (dd 512 x 512: 28.7 ms on one workgroup, 5.0 on 16; qd 128 and 14.9).  Predicted over measured on the present
+// kernels, variant 1, T = 1, 2, 4, 8, 16, 16 x 16 to 512 x 512 and 512 x 64, 200 x 20, 384 x 300: a problem alone
+// 0.81 to 1.28, a device full of equal ones 0.63 to 1.18 (tall problems and those below 64 x 64 on large teams
+// take the longest); variants 0 and 2 take up to 60 and 150 % longer than variant 1.  (Constants fitted to the full
+// device instead gave slower plans where it is not full: qd, 200 problems of up to 96 x 96 1292 -> 1414 us, dd, 16 of
+// up to 512 x 512 4623 -> 4753, and the two large batches above within 1 %.)
 struct BatchCost {
     double one, chain, shared;  // T = 1; T > 1: chain + shared / T
 };
