@@ -107,8 +107,8 @@ int mdls_finalize(void);
  *   MDLS_TUNE_CPANEL           the complex QR's tile panels: 0 one launch per panel column;
  *                              1 one persistent launch per panel (one workgroup per column, the
  *                              columns handed on through device memory); 2 (default) persistent,
- *                              but a launch per column for double with m <= 256 or tile < 32 (the faster
- *                              form of each on MI355X).  The persistent form takes the reflector
+ *                              but a launch per column for double with m <= 256 or tile < 32 and
+ *                              for dd with tile < 3 (the faster form of each on MI355X).  The persistent form takes the reflector
  *                              scalars in another (equivalent) order, so results differ in the
  *                              last bits
  * mdls_set_tuning returns 0, -1 for an unknown option, -2 for a value out of range;

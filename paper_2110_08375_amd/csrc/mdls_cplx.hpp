@@ -1270,9 +1270,12 @@ int cqr_t(int m, int n, int tile, double *A, int lda, double *T, int ldt, void *
     // 549 against 614 us, 512 3.69 / 4.59 ms, 2000 x 64 0.79 / 1.31 ms; qd 64 1.84 / 2.47, 512 15.2 / 20.9 ms;
     // double (tile 32 and 64) 1024 x 512 2.82 / 3.00, 4000 x 64 0.64 / 1.28, 512 2.55 / 2.61 ms, but 64 347 /
     // 331 us and (QR, tile 8) 1024 7.54 / 7.25 ms: a double column of up to 256 rows is one row a thread and a
-    // launch no slower than the hand-off, and a narrow panel's few launches weigh no more than its own two
+    // launch no slower than the hand-off, and a narrow panel's few launches weigh no more than its own two.
+    // dd tiles of one or two columns for the same reason (QR 300 x 60: tile 1 1.32 / 1.11 ms, 2 0.89 / 0.84, 3 0.70 /
+    // 0.70, 4 0.60 / 0.63); qd 300 x 60 tile 1 2.65 / 2.70, od 10.4 / 11.6 ms
     const Tuning tu = tuning();
-    const bool use = tu.cpanel == 1 || (tu.cpanel == 2 && (P >= 2 || (m > kThreads && tile >= 32)));
+    const bool use = tu.cpanel == 1 ||
+                     (tu.cpanel == 2 && (P >= 4 || (P == 2 && tile >= 3) || (P == 1 && m > kThreads && tile >= 32)));
     const bool fits = use && cpanel_capacity<P>() >= tile;
     MDLS_LAUNCH("k_zero", P, 0, k_zero_u32, dim3(1), dim3(64), s, (unsigned *)err, 1);
     bool persisted = false;
@@ -1284,9 +1287,10 @@ int cqr_t(int m, int n, int tile, double *A, int lda, double *T, int ldt, void *
             const CPersistArgs ca{A, (long)lda, psa, m, kt, beta, (long)n, (double *)(w + L.px), (long)m * tile,
                                   (double *)(w + L.pr), err, tu.spin_limit};
             const long nx = 2L * P * m * tile, nr = 4L * P * tile;
-            MDLS_LAUNCH("k_cpanel_init", P, 0, k_cpanel_init, dim3((unsigned)std::min((nx + kThreads * 4 - 1) / (kThreads * 4), 512L)),
-                        dim3(kThreads), s, (unsigned long long *)ca.xs, nx,
-                        (unsigned long long *)(ca.rec + 4L * P * kt), nr);
+            if (tile > 1)  // a panel of one column hands nothing on
+                MDLS_LAUNCH("k_cpanel_init", P, 0, k_cpanel_init, dim3((unsigned)std::min((nx + kThreads * 4 - 1) / (kThreads * 4), 512L)),
+                            dim3(kThreads), s, (unsigned long long *)ca.xs, nx,
+                            (unsigned long long *)(ca.rec + 4L * P * kt), nr);
             double work = 0;
             for (int j = 0; j < tile; ++j) work += 8.0 * (h - j) * (tile - j - 1) + 6.0 * (h - j);
             MDLS_LAUNCH_SHM("k_cpanel", P, work, (k_cpanel<P>), dim3(tile), dim3(kThreads),

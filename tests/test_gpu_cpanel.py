@@ -40,3 +40,10 @@ def test_cpanel_empty_word_in_the_input(M, P):
     torch.cuda.synchronize()
     assert int(info.item()) == 0
     assert np.isnan(x.cpu().numpy()).any()
+
+
+@pytest.mark.parametrize("P,m,n,tile", [(2, 40, 12, 1), (2, 40, 12, 2), (2, 40, 12, 3), (4, 40, 9, 1), (8, 24, 5, 1), (4, 40, 9, 3),
+                                        (1, 40, 12, 1)])
+def test_cpanel_narrow_tiles(M, orc, P, m, n, tile):
+    """Tiles of one column, which hand nothing on, and of the few from which dd takes the persistent panel."""
+    check_csolve(M, orc, P, m, n, tile)
