@@ -1027,6 +1027,7 @@ __global__ __launch_bounds__(kThreads) void k_ctrmm(const double *T, long ldt, l
     acc = cacc_from(v);
 #pragma unroll
     for (int k = 0; k < NW - 1; ++k) {
+        if (k + 1 >= tile) break;  // waves past the tile have summed nothing
         const CV<P> o = clds_ld<P>(&sp[(k * 64 + lane) * 2 * P]);
         acc_add(acc.re, o.re);
         acc_add(acc.im, o.im);
@@ -1073,6 +1074,7 @@ __global__ __launch_bounds__(kThreads) void k_cnn_sub(const double *Y, long lda,
     acc = cacc_from(v);
 #pragma unroll
     for (int k = 0; k < NW - 1; ++k) {
+        if (k + 1 >= tile) break;  // waves past the tile have summed nothing
         const CV<P> o = clds_ld<P>(&sp[(k * 64 + lane) * 2 * P]);
         acc_add(acc.re, o.re);
         acc_add(acc.im, o.im);
