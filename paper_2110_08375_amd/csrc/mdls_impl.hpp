@@ -2072,9 +2072,9 @@ __global__ __launch_bounds__(kThreads) void k_bs_upd(const double *Rc, long ldr,
 // columns of each (and the 16 after them): sums over a row stay in the wave.
 // Bound by the chain of nblk steps; the reading of R goes on beside it (the next blocks in flight).  Before,
 // the tiles were inverted in full, b^3/6 multiply-adds each, and every tile took three launches.  n = 128 (tile 32),
-// 1024 (tile 128), 8192 (tile 128), before and now: dd 61, 145, 840 -> 31, 105, 477 us, qd 98, 313, 1693 -> 96, 285,
-// 1298 us; od n = 4096 3724 -> 3159 us (below, by tiles: backsub_by_tiles); qd n = 17920, tile 256, 4058 -> 3196 us (past 256 blocks
-// the later workgroups start when the first end, and read R at 1.6 TB/s).
+// 1024 (tile 128), 8192 (tile 128), before and now: dd 67, 156, 822 -> 34, 103, 458 us, qd 105, 321, 1709 -> 91, 271,
+// 1220 us; od n = 4096, tile 128, 3689 -> 3008 us (smaller ones by tiles: backsub_by_tiles); qd n = 17920, tile 256,
+// 4194 -> 3123 us (past 256 blocks the later workgroups start when the first end, and read R at 1.7 TB/s).
 // AH = 0: the last block's product, its sum, U_j^-1 and another sum all stand between x_{j+1} and x_j.
 // AH = 2: with M_a = U_j^-1 R_{j,j+a}, x_j = z_j - M_2 x_{j+2} - M_1 x_{j+1}, where z_j = U_j^-1 (y_j -
 // sum_{i > j+2} R_ji x_i) is ready before x_{j+2} comes: a step is one exchange, two multiply-adds a thread and
@@ -2564,7 +2564,7 @@ __global__ __launch_bounds__(kThreads) void k_nn_sub_v(const double *Y, long lda
 // A block skips the k where its X is zero.  In the chunks that hold zeros for some of its rows (kTT and kNN,
 // k > i) the products with them are left out too: Z(k, c) may be NaN or Inf, on which row i does not depend.
 // (kTN, kTNo and kGram need no such care: there a NaN Z(k, c) makes all of the product that follows NaN.)
-//  Bound by the FP64 instruction rate: qd, m = n = 1024,
+// Bound by the FP64 instruction rate: qd, m = n = 1024,
 // tile 128, all 1024 columns, 2.31 ms for the eight Y^T B, 2.17 for B -= Y U and 0.54 for T S, 72 to
 // 77 % of that rate for the first two (one wave per (l, c), one thread per row and one thread per (i, c)
 // before, 64 columns at a time: 4.66, 9.77 and 10.2 ms).
