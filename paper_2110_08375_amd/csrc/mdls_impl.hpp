@@ -2694,7 +2694,8 @@ __global__ __launch_bounds__(kThreads) void k_gemm(GemmArgs g)
                 }
             }
         };
-        if ((MODE == kTT || MODE == kNN) && k0 + KC > i0 + 1)
+        // od in one form: the test is nothing beside its multiply-adds, and two forms take it to one wave per SIMD
+        if ((MODE == kTT || MODE == kNN) && (P >= 8 || k0 + KC > i0 + 1))
             chunk(std::true_type{});
         else
             chunk(std::false_type{});
